@@ -18,6 +18,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <thread>
 #include <vector>
 
@@ -185,7 +186,9 @@ tn_status run_sub(std::vector<Inst>& ins, const SubBatch& sb, const tn_contract_
     std::vector<uint8_t> init(size_t(std::max<int64_t>(init_total, 1)), 0);
     int max_level = 0;
     for (int32_t i : sb.ids) {
-        fill_init(ins[i].net, ins[i].plan, ins[i].el(), init.data() + ins[i].init_off);
+        std::vector<int32_t> all(size_t(ins[i].plan.n_init));
+        std::iota(all.begin(), all.end(), 0);
+        fill_init(ins[i].net, ins[i].plan, all, ins[i].plan.init_off, ins[i].el(), init.data() + ins[i].init_off);
         for (const Step& st : ins[i].plan.steps) max_level = std::max(max_level, st.level);
     }
     std::vector<std::vector<BItem>> wave_items(size_t(max_level) + 1);
@@ -199,7 +202,7 @@ tn_status run_sub(std::vector<Inst>& ins, const SubBatch& sb, const tn_contract_
         std::vector<KernelClass> cls(I.plan.steps.size());
         for (size_t k = 0; k < cls.size(); ++k)
             cls[k] = small_step(I.plan.steps[k]) ? KC_BATCH : choose_class(I.plan.steps[k], I.el(), o->flags);
-        I.dig = digit_plan(I.plan, cls, I.el());
+        I.dig = digit_plan(I.plan.steps, I.plan.rank.size(), cls, I.el());
         char* ib = base + I.init_off;
         for (int32_t k = 0; k < int32_t(I.plan.steps.size()); ++k) {
             const Step& st = I.plan.steps[k];
@@ -426,7 +429,9 @@ extern "C" tn_status tn_count_batch(const tn_formula* fs, int32_t n, tn_order_ki
         I.res.assign(size_t(I.R.u64 ? 0 : I.R.k), 0);
         if (I.plan.n_init == 0 || I.plan.steps.empty()) {
             // empty network or a single scalar tensor: no device work
-            uint64_t v = I.plan.n_init == 0 ? 1 : init_entry(I.net.t[size_t(I.plan.root)], {}, 0);
+            std::vector<uint64_t> one(1, 1);
+            if (I.plan.n_init != 0) init_entries(I.net.t[size_t(I.plan.root)], {}, one);
+            const uint64_t v = one[0];
             I.u64v = v;
             for (int q = 0; q < int(I.res.size()); ++q) I.res[size_t(q)] = uint32_t(v % I.R.primes[size_t(q)]);
             I.host_only = true;

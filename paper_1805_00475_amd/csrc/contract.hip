@@ -22,6 +22,7 @@
 #include "mfma.hpp"
 #include "profile.hpp"
 #include "launch.hpp"
+#include "pinned.hpp"
 #include "tune.hpp"
 
 namespace tn {
@@ -373,24 +374,24 @@ KernelClass choose_class(const Step& st, int el, int flags) {
     return KC_GENERIC;
 }
 
-std::vector<uint8_t> digit_plan(const Plan& plan, const std::vector<KernelClass>& cls, int el) {
-    const size_t n = plan.steps.size();
+std::vector<uint8_t> digit_plan(const std::vector<Step>& steps, size_t n_ids, const std::vector<KernelClass>& cls,
+                                int el) {
+    const size_t n = steps.size();
     std::vector<uint8_t> out_dig(n, 0), dig(n, 0);
     if (el != EL_U32) return dig;  // int8 residues are the matrix-core operands as they are
-    const size_t ids = size_t(plan.n_init) + n;
-    std::vector<int32_t> prod(ids, -1), cons(ids, -1);
+    std::vector<int32_t> prod(n_ids, -1), cons(n_ids, -1);
     for (size_t k = 0; k < n; ++k) {
-        const Step& st = plan.steps[k];
+        const Step& st = steps[k];
         prod[size_t(st.out)] = int32_t(k);
         cons[size_t(st.a)] = int32_t(k);
         cons[size_t(st.b)] = int32_t(k);
     }
     for (size_t k = 0; k < n; ++k) {
-        const int32_t c = cons[size_t(plan.steps[k].out)];
+        const int32_t c = cons[size_t(steps[k].out)];
         out_dig[k] = cls[k] == KC_MFMA && c >= 0 && cls[size_t(c)] == KC_MFMA;
     }
     for (size_t k = 0; k < n; ++k) {
-        const Step& st = plan.steps[k];
+        const Step& st = steps[k];
         const int32_t pa = prod[size_t(st.a)], pb = prod[size_t(st.b)];
         dig[k] = uint8_t((out_dig[k] ? 4 : 0) | (pa >= 0 && out_dig[size_t(pa)] ? 1 : 0) |
                          (pb >= 0 && out_dig[size_t(pb)] ? 2 : 0));
@@ -512,58 +513,36 @@ hipError_t launch_step(const Step& st0, int el, int flags, const uint32_t* prime
     return hipGetLastError();
 }
 
-// Value of one initial tensor entry x in the plan's bit order ``layout``
-// (Eq. 3, Eq. 4, Eq. 6, parity; a negated index is reversed, Sec. 2.1; a
-// table lists its entries by its own bond order).
-uint64_t init_entry(const InitTensor& t, const std::vector<int32_t>& pos, uint64_t x) {
-    const int r = int(t.bonds.size());
-    if (t.kind == T_TABLE) {
-        uint64_t own = 0;
-        for (int k = 0; k < r; ++k) own |= ((x >> pos[k]) & 1) << k;
-        return t.table[size_t(own)];
+// One initial tensor of a plan in its layout at ``out``: entries as they are,
+// or reduced modulo ``mod`` (centred for int8 planes).
+void put_init(const InitTensor& t, const std::vector<int32_t>& layout, int el, const uint32_t* mod, uint8_t* out,
+              std::vector<uint64_t>& tmp) {
+    init_entries(t, layout, tmp);
+    for (size_t x = 0; x < tmp.size(); ++x) {
+        const uint64_t v = tmp[x];
+        if (el == EL_U64) {
+            reinterpret_cast<uint64_t*>(out)[x] = v;
+        } else if (el == EL_I8) {
+            int32_t c = int32_t(v);
+            if (mod) {
+                const int32_t m = int32_t(*mod), rr = int32_t(v % uint64_t(m));
+                c = rr > m / 2 ? rr - m : rr;
+            }
+            reinterpret_cast<int8_t*>(out)[x] = int8_t(c);
+        } else {
+            reinterpret_cast<uint32_t*>(out)[x] = uint32_t(mod ? v % *mod : v);
+        }
     }
-    if (t.kind == T_COPY) {
-        if (r == 0) return 2;  // a variable in no clause: both values count
-        const uint64_t all = (r >= 64) ? ~0ull : ((uint64_t(1) << r) - 1);
-        return (x == 0 || x == all) ? 1 : 0;
-    }
-    int ntrue = 0;
-    for (int k = 0; k < r; ++k) {
-        int bit = int((x >> pos[k]) & 1);
-        ntrue += bit ^ int((t.neg >> k) & 1);
-    }
-    if (t.kind == T_OR) return ntrue >= 1 ? 1 : 0;
-    if (t.kind == T_XOR) return uint64_t(ntrue & 1);
-    return ntrue == 1 ? 1 : 0;
 }
 
 // Initial tensors in plan layout. Without moduli the raw entries are stored
 // (entries of at most 127 are valid residues in every plane); with ``mod``
-// (one modulus) each entry is reduced: centred for int8 planes.
-void fill_init(const Network& net, const Plan& plan, int el, uint8_t* host, const uint32_t* mod) {
-    for (int32_t i = 0; i < plan.n_init; ++i) {
-        const InitTensor& t = net.t[i];
-        const auto& L = plan.layout[i];
-        std::vector<int32_t> pos(t.bonds.size());
-        for (size_t k = 0; k < t.bonds.size(); ++k)
-            pos[k] = int32_t(std::find(L.begin(), L.end(), t.bonds[k]) - L.begin());
-        const uint64_t n = uint64_t(1) << t.bonds.size();
-        for (uint64_t x = 0; x < n; ++x) {
-            uint64_t v = init_entry(t, pos, x);
-            if (el == EL_U64) {
-                reinterpret_cast<uint64_t*>(host)[plan.init_off[i] + x] = v;
-            } else if (el == EL_I8) {
-                int32_t c = int32_t(v);
-                if (mod) {
-                    const int32_t m = int32_t(*mod), rr = int32_t(v % uint64_t(m));
-                    c = rr > m / 2 ? rr - m : rr;
-                }
-                reinterpret_cast<int8_t*>(host)[plan.init_off[i] + x] = int8_t(c);
-            } else {
-                reinterpret_cast<uint32_t*>(host)[plan.init_off[i] + x] = uint32_t(mod ? v % *mod : v);
-            }
-        }
-    }
+// (one modulus) each entry is reduced.
+void fill_init(const Network& net, const Plan& plan, const std::vector<int32_t>& ids,
+               const std::vector<int64_t>& off, int el, uint8_t* host, const uint32_t* mod) {
+    std::vector<uint64_t> tmp;
+    for (size_t k = 0; k < ids.size(); ++k)
+        put_init(net.t[size_t(ids[k])], plan.layout[size_t(ids[k])], el, mod, host + off[k] * elem_size(el), tmp);
 }
 
 // Whether the initial entries must be reduced per residue plane: an int8
@@ -606,9 +585,51 @@ tn_status resolve(const Plan& plan, const tn_contract_opts* o, Resolved& r) {
 
 int64_t align256(int64_t b) { return (b + 255) / 256 * 256; }
 
+namespace {
+
+// Workspace of an Exec: [arena of every plane][scratch of every plane]
+// [programs' blob][initial tensors its steps read, one region or one per plane].
+struct Layout {
+    bool pp;           // initial tensors reduced per plane
+    bool wide;         // the programs' initial entries as 32-bit words
+    int64_t blob, init, arena;  // bytes (init, arena: of one plane)
+    int64_t bytes(int64_t G) const {
+        return blob + (pp ? G : 1) * init + G * (arena + kScratchPerPrime);
+    }
+    // planes that fit ws bytes (0: not one)
+    int64_t planes(int64_t ws) const {
+        if (bytes(1) > ws) return 0;
+        return (ws - blob - (pp ? 0 : init)) / (arena + kScratchPerPrime + (pp ? init : 0));
+    }
+};
+
+Layout layout_of(const Plan& plan, const Exec& ex, const Resolved& R) {
+    Layout l{};
+    l.pp = init_per_plane(plan, R);
+    l.wide = plan.max_entry > 127;
+    l.blob = ex.progs.empty() ? 0 : blob_bytes(ex, l.wide);
+    l.init = align256(ex.init_elems * int64_t(R.es()));
+    l.arena = align256(ex.arena_elems * int64_t(R.es()));
+    return l;
+}
+
+// The plan's fused execution for this arithmetic (its own, or built into
+// ``own``), or step by step with TN_FLAG_GENERIC_ONLY.
+const Exec* exec_of(const Plan& plan, const Resolved& R, int flags, Exec& own) {
+    if (flags & TN_FLAG_GENERIC_ONLY) {
+        plain_exec(plan, own);
+        return &own;
+    }
+    if (const Exec* e = plan_exec(plan, R.es())) return e;
+    build_exec(plan, R.es(), own);
+    return &own;
+}
+
+}  // namespace
+
 // Runs the plan; fills residues (RNS) or *u64v (U64).
 tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,
-                   std::vector<uint32_t>& residues, uint64_t* u64v) {
+                   std::vector<uint32_t>& residues, uint64_t* u64v, bool pinned) {
     const int el = R.u64 ? EL_U64 : R.i8 ? EL_I8 : EL_U32;
     const size_t es = size_t(R.es());
     residues.assign(R.u64 ? 0 : R.k, 0);
@@ -619,74 +640,112 @@ tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts*
         return TN_OK;
     }
     if (plan.steps.empty()) {
-        const InitTensor& t = net.t[plan.root];
-        uint64_t v = init_entry(t, {}, 0);
+        std::vector<uint64_t> one;
+        init_entries(net.t[plan.root], {}, one);
+        const uint64_t v = one[0];
         if (R.u64) *u64v = v;
         for (int i = 0; i < R.k && !R.u64; ++i) residues[i] = uint32_t(v % R.primes[i]);
         return TN_OK;
     }
     if (!o || !o->workspace) return TN_EINVAL;
-    // initial tensors: one region for every plane, or one per plane of a
-    // group when an entry needs reducing modulo each plane's modulus
-    const bool pp = init_per_plane(plan, R);
-    const int64_t init_bytes = align256(plan.init_elems * int64_t(es));
-    const int64_t arena_bytes = align256(plan.arena_elems * int64_t(es));
-    const int64_t arena_elems = arena_bytes / int64_t(es);
     const int64_t ws = int64_t(o->workspace_bytes);
-    if (init_bytes + arena_bytes + kScratchPerPrime > ws) return TN_ETOOBIG;
-    int G = pp ? int(ws / (init_bytes + arena_bytes + kScratchPerPrime))
-               : int((ws - init_bytes) / (arena_bytes + kScratchPerPrime));
-    G = std::min({G, R.k, kMaxGroup});
-    if (o->prime_group > 0) G = std::min(G, int(o->prime_group));
-    G = std::max(G, 1);
+    Exec own, plain;
+    const Exec* ex = exec_of(plan, R, o->flags, own);
+    Layout lay = layout_of(plan, *ex, R);
+    const int64_t want = std::min<int64_t>({int64_t(R.k), int64_t(kMaxGroup),
+                                            o->prime_group > 0 ? int64_t(o->prime_group) : int64_t(kMaxGroup)});
+    int64_t fit = std::min(lay.planes(ws), want);
+    if (fit < want && !ex->progs.empty()) {
+        // the fused layout keeps every program's result from the start: a
+        // tight workspace may hold more planes step by step
+        plain_exec(plan, plain);
+        const Layout pl = layout_of(plan, plain, R);
+        const int64_t pf = std::min(pl.planes(ws), want);
+        if (pf > fit) {
+            ex = &plain;
+            lay = pl;
+            fit = pf;
+        }
+    }
+    if (fit < 1) return TN_ETOOBIG;
+    const int G = int(fit);
+    const bool pp = lay.pp;
+    const int64_t init_bytes = lay.init, arena_elems = lay.arena / int64_t(es);
     hipStream_t stream = static_cast<hipStream_t>(o->stream);
     char* base = static_cast<char*>(o->workspace);
-    char* init_base = base;
-    char* arena_base = base + (pp ? int64_t(G) : 1) * init_bytes;
-    char* scratch = arena_base + int64_t(G) * arena_bytes;
+    char* arena_base = base;
+    char* scratch = arena_base + int64_t(G) * lay.arena;
+    char* blob_base = scratch + int64_t(G) * kScratchPerPrime;
+    char* init_base = blob_base + lay.blob;
     const int64_t init_stride = pp ? init_bytes / int64_t(es) : 0;
-    // host images: one region, or one per modulus (held until the end)
-    const int n_img = pp ? R.k : 1;
-    std::vector<uint8_t> host(size_t(init_bytes) * size_t(n_img), 0);
-    for (int q = 0; q < n_img; ++q)
-        fill_init(net, plan, el, host.data() + size_t(q) * size_t(init_bytes), pp ? &R.primes[size_t(q)] : nullptr);
+    // host images: the blob and one region of initial tensors, or one per
+    // modulus (held until the end); a small image goes through a pinned
+    // block, read by an upload kernel (a pageable copy of 32 KB takes 20 us,
+    // the kernel 4)
+    PinnedBlock pin(pinned);
+    const int64_t head = lay.blob + (pp ? 0 : init_bytes);
+    const bool staged = pin.p && head <= int64_t(PinnedPool::kUpload);
+    std::vector<uint8_t> host(size_t((staged ? 0 : head) + (pp ? int64_t(R.k) * init_bytes : 0)), 0);
+    uint8_t* img = staged ? pin.p : host.data();
+    uint8_t* pp_img = host.data() + (staged ? 0 : head);
+    if (staged) std::memset(img, 0, size_t(head));
+    if (lay.blob) fill_blob(net, plan, *ex, lay.wide, img);
+    if (!pp) fill_init(net, plan, ex->init_ids, ex->init_off, el, img + lay.blob);
+    for (int q = 0; pp && q < R.k; ++q)
+        fill_init(net, plan, ex->init_ids, ex->init_off, el, pp_img + int64_t(q) * init_bytes, &R.primes[size_t(q)]);
     Profiler& prof = profiler();
-    hipError_t err = pp ? hipSuccess : hipMemcpyAsync(init_base, host.data(), host.size(), hipMemcpyHostToDevice, stream);
-    // on any failure, drain the stream before the host staging buffer goes away
+    // on any failure, drain the stream before the host staging goes away
     auto fail = [&]() {
         (void)hipStreamSynchronize(stream);
         prof.collect();
         return TN_EHIP;
     };
-    if (err != hipSuccess) return fail();
-    const Step& last = plan.steps.back();
-    std::vector<KernelClass> cls(plan.steps.size());
-    for (size_t k = 0; k < cls.size(); ++k) cls[k] = choose_class(plan.steps[k], el, o->flags);
-    const std::vector<uint8_t> dig = digit_plan(plan, cls, el);
+    const bool root_fused = ex->steps.empty();
+    std::vector<KernelClass> cls(ex->steps.size());
+    for (size_t k = 0; k < cls.size(); ++k) cls[k] = choose_class(ex->steps[k], el, o->flags);
+    const std::vector<uint8_t> dig = digit_plan(ex->steps, plan.rank.size(), cls, el);
+    // a kernel writes the results: to the pinned block, or to scratch from
+    // where each group's are copied
     std::vector<uint64_t> out(size_t(R.k), 0);
+    hipError_t err = hipSuccess;
+    if (head > 0)
+        err = staged ? launch_upload(img, blob_base, head / 16, stream)
+                     : hipMemcpyAsync(blob_base, img, size_t(head), hipMemcpyHostToDevice, stream);
+    if (err != hipSuccess) return fail();
     for (int g0 = 0; g0 < R.k; g0 += G) {
         const int gn = std::min(G, R.k - g0);
-        if (pp) {
+        const uint32_t* mods = R.u64 ? nullptr : R.primes.data() + g0;
+        uint64_t* res = pin.p ? pin.results() + g0 : reinterpret_cast<uint64_t*>(scratch);
+        if (pp && init_bytes > 0) {
             // this group's planes of the initial tensors
-            err = hipMemcpyAsync(init_base, host.data() + size_t(g0) * size_t(init_bytes),
-                                 size_t(gn) * size_t(init_bytes), hipMemcpyHostToDevice, stream);
+            err = hipMemcpyAsync(init_base, pp_img + int64_t(g0) * init_bytes, size_t(gn) * size_t(init_bytes),
+                                 hipMemcpyHostToDevice, stream);
             if (err != hipSuccess) return fail();
         }
-        for (size_t k = 0; k < plan.steps.size(); ++k) {
+        if (!ex->progs.empty()) {
+            prof.cur_rA = prof.cur_rB = prof.cur_s = prof.cur_rC = 0;
+            prof.cur_G = gn;
+            prof.before(stream);
+            err = launch_fused(*ex, el, mods, gn, blob_base, lay.wide, arena_base, arena_elems, res, stream);
+            prof.after_raw(stream, KC_BATCH, double(es) * gn * ex->prog_entries, gn * ex->prog_macs);
+            if (err != hipSuccess) return fail();
+        }
+        for (size_t k = 0; k < ex->steps.size(); ++k) {
             KernelClass kc = KC_GENERIC;
-            err = launch_step(plan.steps[k], el, o->flags, R.u64 ? nullptr : R.primes.data() + g0, gn, init_base,
-                              arena_base, arena_elems, scratch, stream, &kc, -1, dig[k], init_stride);
+            err = launch_step(ex->steps[k], el, o->flags, mods, gn, init_base, arena_base, arena_elems, scratch,
+                              stream, &kc, -1, dig[k], init_stride);
             if (err != hipSuccess) return fail();
         }
-        for (int g = 0; g < gn; ++g) {
-            err = hipMemcpyAsync(&out[g0 + g], arena_base + (g * arena_elems + last.offC) * int64_t(es), es,
-                                 hipMemcpyDeviceToHost, stream);
-            if (err != hipSuccess) return fail();
-        }
+        if (!root_fused)
+            err = launch_gather(el, gn, arena_base, arena_elems, ex->steps.back().offC, res, stream);
+        if (err == hipSuccess && !pin.p)
+            err = hipMemcpyAsync(out.data() + g0, res, size_t(gn) * 8, hipMemcpyDeviceToHost, stream);
+        if (err != hipSuccess) return fail();
     }
     err = hipStreamSynchronize(stream);
     if (err != hipSuccess) return TN_EHIP;
     prof.collect();
+    if (pin.p) std::copy(pin.results(), pin.results() + R.k, out.begin());
     if (R.u64) {
         *u64v = out[0];
     } else if (R.i8) {
@@ -713,11 +772,15 @@ tn_status tn_workspace_bytes(const tn_network* net, const tn_plan* plan, const t
     Resolved R;
     tn_status st = resolve(plan->plan, opts, R);
     if (st != TN_OK) return st;
-    const int64_t es = R.es();
-    int G = (opts && opts->prime_group > 0) ? std::min<int>(opts->prime_group, std::min(R.k, kMaxGroup)) : 1;
-    const int64_t init = align256(plan->plan.init_elems * es);
-    *bytes = size_t((init_per_plane(plan->plan, R) ? int64_t(G) : 1) * init +
-                    int64_t(G) * (align256(plan->plan.arena_elems * es) + kScratchPerPrime));
+    const int G = (opts && opts->prime_group > 0) ? std::min<int>(opts->prime_group, std::min(R.k, kMaxGroup)) : 1;
+    try {
+        Exec own, plain;
+        const Exec* ex = exec_of(plan->plan, R, opts ? opts->flags : 0, own);
+        plain_exec(plan->plan, plain);
+        *bytes = size_t(std::max(layout_of(plan->plan, *ex, R).bytes(G), layout_of(plan->plan, plain, R).bytes(G)));
+    } catch (const std::bad_alloc&) {
+        return TN_ENOMEM;
+    }
     return TN_OK;
 }
 
@@ -733,8 +796,8 @@ tn_status tn_moduli(const tn_plan* plan, const tn_contract_opts* opts, uint32_t*
     return TN_OK;
 }
 
-tn_status tn_contract(const tn_network* net, const tn_plan* plan, const tn_contract_opts* opts, uint32_t* residues,
-                      int32_t residues_cap, uint64_t* u64) {
+static tn_status contract(const tn_network* net, const tn_plan* plan, const tn_contract_opts* opts, uint32_t* residues,
+                          int32_t residues_cap, uint64_t* u64, bool pinned) {
     if (!net || !plan) return TN_EINVAL;
     if (int32_t(net->net.t.size()) != plan->plan.n_init) return TN_EINVAL;
     Resolved R;
@@ -745,7 +808,7 @@ tn_status tn_contract(const tn_network* net, const tn_plan* plan, const tn_contr
     uint64_t v = 0;
     profiler().start(opts && (opts->flags & TN_FLAG_TIMING));
     try {
-        st = run_plan(net->net, plan->plan, opts, R, res, &v);
+        st = run_plan(net->net, plan->plan, opts, R, res, &v, pinned);
     } catch (const std::bad_alloc&) {
         return TN_ENOMEM;
     }
@@ -756,6 +819,11 @@ tn_status tn_contract(const tn_network* net, const tn_plan* plan, const tn_contr
         std::copy(res.begin(), res.end(), residues);
     }
     return TN_OK;
+}
+
+tn_status tn_contract(const tn_network* net, const tn_plan* plan, const tn_contract_opts* opts, uint32_t* residues,
+                      int32_t residues_cap, uint64_t* u64) {
+    return contract(net, plan, opts, residues, residues_cap, u64, true);
 }
 
 tn_status tn_count(const tn_network* net, const tn_plan* plan, const tn_contract_opts* opts, uint32_t* limbs,
@@ -829,7 +897,7 @@ extern "C" tn_status tn_contract_noalloc(const tn_network* net, const tn_plan* p
     o.workspace_bytes = kNoAllocBytes;
     // the plan's init region, arena and scratch must fit the array; run_plan
     // returns TN_ETOOBIG before any device work otherwise
-    return tn_contract(net, plan, &o, residues, residues_cap, u64);
+    return contract(net, plan, &o, residues, residues_cap, u64, false);
 }
 
 extern "C" size_t tn_noalloc_max_bytes(void) { return kNoAllocBytes; }

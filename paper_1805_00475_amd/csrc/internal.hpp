@@ -4,6 +4,7 @@
 #include <array>
 #include <atomic>
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <utility>
 #include <vector>
@@ -55,6 +56,8 @@ struct Step {
     int32_t level = 0;                   // longest chain of steps feeding this one
 };
 
+struct Exec;
+
 struct Plan {
     int32_t n_init = 0;
     int32_t n_vars = 0;
@@ -72,6 +75,10 @@ struct Plan {
     double cost_us = -1;                       // plan_cost, kept by make_plan (-1: not yet)
     bool sketch = false;                       // merges, cost and stats only (sketch_plan)
     tn_plan_stats stats{};
+    // fused execution (fuse.hpp) for entries of exec_es bytes, the plan's
+    // default arithmetic when it was made
+    std::shared_ptr<const Exec> exec;
+    int32_t exec_es = 0;
 };
 
 constexpr int64_t kAlignElems = 64;  // 256 bytes for 32-bit entries
@@ -80,6 +87,7 @@ constexpr int64_t kAlignElems = 64;  // 256 bytes for 32-bit entries
 tn_status build_network(const tn_formula* f, Network& net);
 tn_status build_csp(const tn_csp* c, Network& net);
 tn_status reduce_degree(Network& net, uint32_t flags);
+void init_entries(const InitTensor& t, const std::vector<int32_t>& layout, std::vector<uint64_t>& out);
 
 // order_*.cpp: produce merges (pairs of tensor ids; merge k creates id
 // n_init + k). Every order ends with a single tensor.
@@ -159,8 +167,9 @@ struct Resolved {
     int32_t es() const { return u64 ? 8 : i8 ? 1 : 4; }
 };
 tn_status resolve(const Plan& plan, const tn_contract_opts* o, Resolved& r);
+// pinned: the call may use pinned host staging memory (which it allocates)
 tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,
-                   std::vector<uint32_t>& residues, uint64_t* u64v);
+                   std::vector<uint32_t>& residues, uint64_t* u64v, bool pinned = true);
 
 // crt.cpp
 // primes of the residue path: the largest below kPrimeBound, descending

@@ -6,6 +6,7 @@
 
 #include <vector>
 
+#include "fuse.hpp"
 #include "internal.hpp"
 #include "kernels.hpp"
 #include "profile.hpp"
@@ -38,20 +39,32 @@ KernelClass choose_class(const Step& st, int el, int flags);
 // bits of launch_step, given the class each step runs with. A tensor is
 // written as digit planes when its producer and its consumer both run the
 // matrix-core kernel, which then skips the digit pass on it.
-std::vector<uint8_t> digit_plan(const Plan& plan, const std::vector<KernelClass>& cls, int el);
+std::vector<uint8_t> digit_plan(const std::vector<Step>& steps, size_t n_ids, const std::vector<KernelClass>& cls,
+                                int el);
 
 // Bytes per entry of an element kind (EL_U32, EL_U64, EL_I8 of kernels.hpp).
 int elem_size(int el);
 // Moduli and their reduction constants of G residue planes.
 void fill_moduli(StepArgs& a, const uint32_t* primes, int G);
 
+// Runs an Exec's programs (blob at d_blob, in device memory) for G residue
+// planes: roots go to the arena, the network's scalar, when it is one of the
+// roots, to res[plane] (int8 residues sign-extended).
+hipError_t launch_fused(const Exec& ex, int el, const uint32_t* primes, int G, const void* d_blob, bool wide,
+                        char* arena_base, int64_t arena_elems, uint64_t* res, hipStream_t stream);
+// res[g] = entry off of plane g
+hipError_t launch_gather(int el, int G, const char* arena_base, int64_t arena_elems, int64_t off, uint64_t* res,
+                         hipStream_t stream);
+// dst = src, n16 blocks of 16 bytes (src may be pinned host memory)
+hipError_t launch_upload(const void* src, void* dst, int64_t n16, hipStream_t stream);
+
 // The streaming kernel with 2^nb B rows per thread (autotuner launches).
 hipError_t launch_stream_step(const StepArgs& a, int el, int G, int nb, hipStream_t st);
 
-// Entry x of an initial tensor whose bonds sit at bit positions pos.
-uint64_t init_entry(const InitTensor& t, const std::vector<int32_t>& pos, uint64_t x);
-// Writes every initial tensor of a plan, in plan layout, at its init offset.
-void fill_init(const Network& net, const Plan& plan, int el, uint8_t* host, const uint32_t* mod = nullptr);
+// Writes the initial tensors ids at the entry offsets off, in plan layout
+// (reduced modulo *mod when given).
+void fill_init(const Network& net, const Plan& plan, const std::vector<int32_t>& ids,
+               const std::vector<int64_t>& off, int el, uint8_t* host, const uint32_t* mod = nullptr);
 bool init_per_plane(const Plan& plan, const Resolved& R);
 
 }  // namespace tn

@@ -314,4 +314,36 @@ tn_status build_csp(const tn_csp* c, Network& net) {
     return TN_OK;
 }
 
+// Entries of one initial tensor in the bit order ``layout`` (Eq. 3, Eq. 4,
+// Eq. 6, parity; a negated index is reversed, Sec. 2.1; a table lists its
+// entries by its own bond order).
+void init_entries(const InitTensor& t, const std::vector<int32_t>& layout, std::vector<uint64_t>& out) {
+    const int r = int(t.bonds.size());
+    const uint64_t n = uint64_t(1) << r;
+    out.assign(size_t(n), 0);
+    if (t.kind == T_COPY) {
+        out[0] = r == 0 ? 2 : 1;  // a variable in no clause: both values count
+        out[size_t(n - 1)] = out[0];
+        return;
+    }
+    // layout position of every own index
+    int pos[64];
+    for (int k = 0; k < r; ++k)
+        pos[k] = int(std::find(layout.begin(), layout.end(), t.bonds[size_t(k)]) - layout.begin());
+    if (t.kind == T_TABLE) {
+        for (uint64_t x = 0; x < n; ++x) {
+            uint64_t own = 0;
+            for (int k = 0; k < r; ++k) own |= ((x >> pos[k]) & 1) << k;
+            out[size_t(x)] = t.table[size_t(own)];
+        }
+        return;
+    }
+    uint64_t neg = 0;
+    for (int k = 0; k < r; ++k) neg |= ((t.neg >> k) & 1) << pos[k];
+    for (uint64_t x = 0; x < n; ++x) {
+        const int ntrue = __builtin_popcountll(x ^ neg);
+        out[size_t(x)] = t.kind == T_OR ? ntrue >= 1 : t.kind == T_XOR ? ntrue & 1 : ntrue == 1;
+    }
+}
+
 }  // namespace tn

@@ -14,9 +14,10 @@
 // merged in death order -- which is again the layout C's own consumer needs.
 #include <algorithm>
 #include <cmath>
-#include <map>
 #include <new>
 
+#include "arena.hpp"
+#include "fuse.hpp"
 #include "internal.hpp"
 
 namespace tn {
@@ -24,55 +25,6 @@ namespace tn {
 namespace {
 
 int64_t align_up(int64_t x) { return (x + kAlignElems - 1) / kAlignElems * kAlignElems; }
-
-// First-fit arena over [0, inf) with coalescing free list.
-struct Arena {
-    std::map<int64_t, int64_t> free_;  // offset -> size
-    int64_t top = 0;
-    int64_t high = 0;
-    int64_t alloc(int64_t n) {
-        for (auto it = free_.begin(); it != free_.end(); ++it)
-            if (it->second >= n) {
-                int64_t off = it->first;
-                int64_t rest = it->second - n;
-                free_.erase(it);
-                if (rest > 0) free_[off + n] = rest;
-                return off;
-            }
-        // extend: reuse a free block touching the top
-        int64_t off = top;
-        if (!free_.empty()) {
-            auto last = std::prev(free_.end());
-            if (last->first + last->second == top) {
-                off = last->first;
-                free_.erase(last);
-            }
-        }
-        top = off + n;
-        high = std::max(high, top);
-        return off;
-    }
-    void release(int64_t off, int64_t n) {
-        auto it = free_.emplace(off, n).first;
-        auto nx = std::next(it);
-        if (nx != free_.end() && it->first + it->second == nx->first) {
-            it->second += nx->second;
-            free_.erase(nx);
-        }
-        if (it != free_.begin()) {
-            auto pv = std::prev(it);
-            if (pv->first + pv->second == it->first) {
-                pv->second += it->second;
-                free_.erase(it);
-                it = pv;
-            }
-        }
-        if (it->first + it->second == top) {
-            top = it->first;
-            free_.erase(it);
-        }
-    }
-};
 
 }  // namespace
 
@@ -391,6 +343,11 @@ tn_status make_plan(const Network& net, std::vector<std::pair<int32_t, int32_t>>
         plan.stats.log2_cost = c > 0 ? std::log2(c) : 0.0;
         plan.stats.chosen = chosen;
         plan.stats.fallback = 0;
+        const int mode = default_residue_mode(plan.count_bits);
+        plan.exec_es = mode == RM_U64 ? 8 : mode == RM_SMALL ? 1 : 4;
+        auto ex = std::make_shared<Exec>();
+        build_exec(plan, plan.exec_es, *ex);
+        plan.exec = std::move(ex);
     } catch (const std::bad_alloc&) {
         return TN_ENOMEM;
     }
