@@ -13,8 +13,8 @@
  * a learned scorer) fixes the sequence of pairwise contractions; HIP kernels
  * run them on the GPU. Counts are exact (the paper's floating-point counts
  * lose precision from about 100 vertices, Sec. 3.2): 64-bit unsigned
- * arithmetic while the count is below 2^64 (at most 63 boolean variables);
- * otherwise residues modulo the fewest small pairwise coprime moduli
+ * arithmetic while the count is below 2^64 (at most 63 boolean variables;
+ * plans of wide steps get there through the residues below); otherwise residues modulo the fewest small pairwise coprime moduli
  * (<= 255, one signed byte per residue) whose product exceeds twice the
  * largest possible count, or, beyond about 332 bits, modulo 16-bit primes;
  * the residues are combined on the host by the Chinese remainder theorem at

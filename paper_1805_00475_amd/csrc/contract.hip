@@ -627,9 +627,9 @@ const Exec* exec_of(const Plan& plan, const Resolved& R, int flags, Exec& own) {
 
 }  // namespace
 
-// Runs the plan; fills residues (RNS) or *u64v (U64).
-tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,
-                   std::vector<uint32_t>& residues, uint64_t* u64v, bool pinned) {
+// Runs the plan in the arithmetic of R; fills residues (RNS) or *u64v (U64).
+static tn_status run_planes(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,
+                            std::vector<uint32_t>& residues, uint64_t* u64v, bool pinned) {
     const int el = R.u64 ? EL_U64 : R.i8 ? EL_I8 : EL_U32;
     const size_t es = size_t(R.es());
     residues.assign(R.u64 ? 0 : R.k, 0);
@@ -760,6 +760,34 @@ tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts*
     return TN_OK;
 }
 
+bool residue_route(const Plan& plan, const Resolved& R, int flags, Resolved& rr) {
+    if (!R.u64 || !counts_by_residues(plan) || (flags & (TN_FLAG_GENERIC_ONLY | TN_FLAG_NO_MFMA))) return false;
+    rr = Resolved{};
+    rr.i8 = true;
+    rr.k = small_moduli_needed(plan.count_bits);
+    const auto& M = small_moduli();
+    rr.primes.assign(M.begin(), M.begin() + rr.k);
+    return true;
+}
+
+tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,
+                   std::vector<uint32_t>& residues, uint64_t* u64v, bool pinned) {
+    Resolved rr;
+    if (!o || !residue_route(plan, R, o->flags, rr)) return run_planes(net, plan, o, R, residues, u64v, pinned);
+    // a 64-bit plane's workspace holds several residue planes: the option to
+    // keep few of them resident is about that one plane
+    tn_contract_opts ro = *o;
+    ro.prime_group = 0;
+    std::vector<uint32_t> res, limbs;
+    const tn_status st = run_planes(net, plan, &ro, rr, res, nullptr, pinned);
+    if (st == TN_ETOOBIG) return run_planes(net, plan, o, R, residues, u64v, pinned);
+    if (st != TN_OK) return st;
+    crt_limbs(res.data(), rr.primes.data(), rr.k, limbs);
+    residues.clear();
+    *u64v = limbs[0] | (limbs.size() > 1 ? uint64_t(limbs[1]) << 32 : 0);
+    return TN_OK;
+}
+
 }  // namespace tn
 
 using namespace tn;
@@ -777,7 +805,14 @@ tn_status tn_workspace_bytes(const tn_network* net, const tn_plan* plan, const t
         Exec own, plain;
         const Exec* ex = exec_of(plan->plan, R, opts ? opts->flags : 0, own);
         plain_exec(plan->plan, plain);
-        *bytes = size_t(std::max(layout_of(plan->plan, *ex, R).bytes(G), layout_of(plan->plan, plain, R).bytes(G)));
+        int64_t need = std::max(layout_of(plan->plan, *ex, R).bytes(G), layout_of(plan->plan, plain, R).bytes(G));
+        Resolved rr;
+        if (residue_route(plan->plan, R, opts ? opts->flags : 0, rr)) {
+            Exec rown;
+            const Exec* rex = exec_of(plan->plan, rr, 0, rown);
+            need = std::max(need, layout_of(plan->plan, *rex, rr).bytes(std::min(rr.k, kMaxGroup)));
+        }
+        *bytes = size_t(need);
     } catch (const std::bad_alloc&) {
         return TN_ENOMEM;
     }

@@ -167,6 +167,21 @@ struct Resolved {
     int32_t es() const { return u64 ? 8 : i8 ? 1 : 4; }
 };
 tn_status resolve(const Plan& plan, const tn_contract_opts* o, Resolved& r);
+// Whether a 64-bit contraction of the plan runs in small moduli instead
+// (int8 matrix cores, one product per multiply-add and modulus) and is
+// recombined by CRT: the same count, since it is below 2^count_bits.
+// 64-bit multiply-adds have no matrix instruction. Below this many
+// multiply-adds both take the time of their launches; measured on 3-CNF
+// formulas, 64-bit against residues: 2e7 multiply-adds 0.128 / 0.116 ms, 3e7
+// 0.124 / 0.131 ms, 3e8 0.48 / 0.15 ms, 5e9 4.1 / 0.76 ms, 1.4e11 116.6 / 3.0 ms.
+constexpr double kResidueMacs = 33554432.0;  // 2^25
+inline bool counts_by_residues(const Plan& plan) {
+    return plan.count_bits <= 63 && plan.stats.macs >= kResidueMacs;
+}
+// The moduli of that route for a contraction resolved to 64-bit counts;
+// false: it stays as it is.
+bool residue_route(const Plan& plan, const Resolved& R, int flags, Resolved& rr);
+// Runs the plan; fills residues (RNS) or *u64v (U64).
 // pinned: the call may use pinned host staging memory (which it allocates)
 tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,
                    std::vector<uint32_t>& residues, uint64_t* u64v, bool pinned = true);

@@ -344,7 +344,7 @@ tn_status make_plan(const Network& net, std::vector<std::pair<int32_t, int32_t>>
         plan.stats.chosen = chosen;
         plan.stats.fallback = 0;
         const int mode = default_residue_mode(plan.count_bits);
-        plan.exec_es = mode == RM_U64 ? 8 : mode == RM_SMALL ? 1 : 4;
+        plan.exec_es = mode == RM_WIDE ? 4 : mode == RM_SMALL || counts_by_residues(plan) ? 1 : 8;
         auto ex = std::make_shared<Exec>();
         build_exec(plan, plan.exec_es, *ex);
         plan.exec = std::move(ex);
