@@ -4,9 +4,18 @@
 // are the candidate pairs of one state of a teacher's order, some of them
 // marked as merges the teacher makes next; per group
 //   L = log sum_all exp(y) - log sum_pos exp(y),
-// averaged over groups. Gradients go through the three layers by hand;
-// parameter gradients are summed over rows with float atomics. Adam updates
-// the packed parameters in place. Every buffer belongs to the caller.
+// averaged over groups. Gradients go through the three layers by hand. Adam
+// updates the packed parameters in place. Every buffer belongs to the caller.
+//
+// The 128 x 128 products (h1 W2^T, dZ2 W2, dZ2^T h1) run on the matrix cores in
+// fp32 (v_mfma_f32_16x16x4: fp32 products and sums, lane l holding row or
+// column l % 16 at K index l / 16 of a step), 16 x 16 blocks per wave, with the
+// weights of a wave's 32 columns kept in registers over all of its rows. What
+// is left bounds a training step: six launches, each little more than its
+// latency at 13 k rows (the longest: k_back1 22, k_forward 17, k_back2 13 us). Measured (MI355X, 13.4 k rows, 64 groups): forward +
+// backward + Adam 716 us with one-output-per-thread products and atomic sums
+// of every weight gradient, 61 us now; forward of 201 rows 37.7 us in three
+// launches, 6.8 us in one.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -20,83 +29,115 @@ namespace {
 
 constexpr int F = kFeatures, H = kHidden;
 
-__global__ __launch_bounds__(256) void k_fill(float* p, int64_t n, float v) {
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
-        p[i] = v;
-}
+typedef float v4f __attribute__((ext_vector_type(4)));
+// four floats at any 4-byte aligned address
+typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// layer 1: one thread per (row, unit)
-__global__ __launch_bounds__(256) void k_fwd1(const float* P, const float* X, int64_t n, float* H1) {
-    __shared__ float w[H * F + H];
-    for (int t = threadIdx.x; t < H * F + H; t += blockDim.x) w[t] = P[kOffW1 + t];  // W1 then b1
-    __syncthreads();
-    const int64_t total = n * H;
-    for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < total; e += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t i = e / H;
-        const int j = int(e % H);
-        float a = w[H * F + j];
+constexpr int kThreads = 256;  // 4 waves, 32 of the 128 columns each
+constexpr int kPad = H + 4;    // LDS row of a 128-wide tile read four floats at a time
+constexpr int kRec = H * H + 2 * H + 1;  // gradients of W2, b2, w3, b3, packed as in the parameters
+static_assert(kOffB2 == kOffW2 + H * H && kOffW3 == kOffB2 + H && kOffB3 == kOffW3 + H, "packing");
+
+// acc[rb][cb] += rows of a tile (LDS, kPad floats each) times the wave's
+// fragments w[cb][kb]: lane l's floats j hold K index 16 kb + 4 (l / 16) + j
+template <int RT>
+__device__ __forceinline__ void mul_tile(const float (&tile)[16 * RT][kPad], const v4f (&w)[2][8], int lane,
+                                         v4f (&acc)[RT][2]) {
+    const int fr = lane & 15, q = lane >> 4;
 #pragma unroll
-        for (int k = 0; k < F; ++k) a += w[j * F + k] * X[i * F + k];
-        H1[e] = a > 0.0f ? a : 0.0f;
-    }
+    for (int kb = 0; kb < 8; ++kb)
+#pragma unroll
+        for (int rb = 0; rb < RT; ++rb) {
+            const v4f a = *reinterpret_cast<const v4f*>(&tile[16 * rb + fr][16 * kb + 4 * q]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+                    acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], w[cb][kb][j], acc[rb][cb], 0, 0, 0);
+        }
 }
 
-// out[i][j] = relu?(sum_k In[i][k] M[j][k] + bias[j]) with M = W2 (transpose
-// = false: forward) or out[i][k] = sum_j In[i][j] W2[j][k] masked by
-// Mask[i][k] > 0 (backward through layer 2). 32 rows per block, the weight
-// matrix staged in LDS in the orientation that keeps reads conflict-free.
-template <bool FORWARD>
-__global__ __launch_bounds__(256) void k_dense(const float* P, const float* In, const float* Mask, int64_t n,
-                                               float* Out) {
-    __shared__ float wt[H * H];  // wt[k][j]: contribution of input k to output j
-    __shared__ float rows[32][H];
-    const float* W2 = P + kOffW2;
-    for (int t = threadIdx.x; t < H * H; t += blockDim.x) {
-        const int a = t / H, b = t % H;
-        // forward: out j = sum_k W2[j][k] in k  -> wt[k][j] = W2[j][k]
-        // backward: out k = sum_j W2[j][k] in j -> wt[j][k] = W2[j][k]
-        if (FORWARD)
-            wt[b * H + a] = W2[a * H + b];
-        else
-            wt[a * H + b] = W2[a * H + b];
+// All three layers of 16 RT rows per tile.
+template <int RT>
+__global__ __launch_bounds__(kThreads) void k_forward(const float* P, const float* X, int64_t n, float* H1, float* H2,
+                                                      float* y) {
+    __shared__ __align__(16) float t1[16 * RT][kPad];
+    __shared__ float sx[16 * RT][F];
+    __shared__ float ys[16 * RT][4];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, fr = lane & 15, q = lane >> 4;
+    const int j = t & (H - 1);
+    float w1[F];
+#pragma unroll
+    for (int k = 0; k < F; ++k) w1[k] = P[kOffW1 + j * F + k];
+    const float b1 = P[kOffB1 + j];
+    v4f wf[2][8];
+    float b2[2], w3[2];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+        const int col = 32 * w + 16 * cb + fr;
+#pragma unroll
+        for (int kb = 0; kb < 8; ++kb) wf[cb][kb] = *reinterpret_cast<const v4u*>(P + kOffW2 + col * H + 16 * kb + 4 * q);
+        b2[cb] = P[kOffB2 + col];
+        w3[cb] = P[kOffW3 + col];
     }
-    const int j = threadIdx.x & (H - 1);
-    const int r0 = threadIdx.x >> 7;  // 0 or 1
-    for (int64_t base = int64_t(blockIdx.x) * 32; base < n; base += int64_t(gridDim.x) * 32) {
+    const int64_t tiles = (n + 16 * RT - 1) / (16 * RT);
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t base = tile * (16 * RT);
         __syncthreads();
-        for (int t = threadIdx.x; t < 32 * H; t += blockDim.x) {
-            const int64_t i = base + t / H;
-            rows[t / H][t % H] = i < n ? In[i * H + t % H] : 0.0f;
-        }
+        for (int e = t; e < 16 * RT * F; e += kThreads) sx[e / F][e % F] = base + e / F < n ? X[base * F + e] : 0.0f;
         __syncthreads();
-        for (int r = r0; r < 32; r += 2) {
+#pragma unroll 4
+        for (int r = t >> 7; r < 16 * RT; r += 2) {
             const int64_t i = base + r;
-            if (i >= n) break;
-            float a = FORWARD ? P[kOffB2 + j] : 0.0f;
-#pragma unroll 8
-            for (int k = 0; k < H; ++k) a += rows[r][k] * wt[k * H + j];
-            if (FORWARD) {
-                Out[i * H + j] = a > 0.0f ? a : 0.0f;
-            } else {
-                Out[i * H + j] = Mask[i * H + j] > 0.0f ? a : 0.0f;
+            float h = 0.0f;
+            if (i < n) {
+                float a = b1;
+#pragma unroll
+                for (int k = 0; k < F; ++k) a += w1[k] * sx[r][k];
+                h = a > 0.0f ? a : 0.0f;
+                H1[i * H + j] = h;
             }
+            t1[r][j] = h;
         }
+        __syncthreads();
+        v4f acc[RT][2];
+#pragma unroll
+        for (int rb = 0; rb < RT; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = v4f{b2[cb], b2[cb], b2[cb], b2[cb]};
+        mul_tile<RT>(t1, wf, lane, acc);
+#pragma unroll
+        for (int rb = 0; rb < RT; ++rb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * rb + 4 * q + v;
+                const int64_t i = base + r;
+                float s = 0.0f;
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    const float a = acc[rb][cb][v];
+                    const float h = a > 0.0f ? a : 0.0f;
+                    if (i < n) H2[i * H + 32 * w + 16 * cb + fr] = h;
+                    s += h * w3[cb];
+                }
+                for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
+                if (fr == 0) ys[r][w] = s;
+            }
+        __syncthreads();
+        if (t < 16 * RT && base + t < n) y[base + t] = ((ys[t][0] + ys[t][1]) + (ys[t][2] + ys[t][3])) + P[kOffB3];
     }
 }
 
-// layer 3: one wavefront per row
-__global__ __launch_bounds__(256) void k_fwd3(const float* P, const float* H2, int64_t n, float* y) {
-    const int lane = threadIdx.x & 63;
-    for (int64_t i = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6); i < n; i += int64_t(gridDim.x) * 4) {
-        float a = P[kOffW3 + lane] * H2[i * H + lane] + P[kOffW3 + lane + 64] * H2[i * H + lane + 64];
-        for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
-        if (lane == 0) y[i] = a + P[kOffB3];
-    }
+// what atomics add to starts at zero
+__global__ __launch_bounds__(256) void k_zero(float* grad, int n, float* loss) {
+    for (int i = threadIdx.x; i < n; i += 256) grad[i] = 0.0f;
+    if (threadIdx.x == 0) *loss = 0.0f;
 }
 
-// listwise loss per group: dy = (softmax_all - softmax_pos) / G
+// listwise loss per group: dy = (softmax_all - softmax_pos) / G; the group's loss
+// to loss_of[g], or added to *loss without such a place
 __global__ __launch_bounds__(256) void k_loss(const float* y, const uint8_t* lab, const int32_t* groups, int32_t G,
-                                              float* dy, float* loss) {
+                                              float* dy, float* loss, float* loss_of) {
     __shared__ float red[3][4];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     for (int32_t g = blockIdx.x; g < G; g += gridDim.x) {
@@ -131,73 +172,209 @@ __global__ __launch_bounds__(256) void k_loss(const float* y, const uint8_t* lab
             const float d = ex / sa - (lab[i] && sp > 0.0f ? ex / sp : 0.0f);
             dy[i] = sp > 0.0f ? d * inv_g : 0.0f;
         }
-        if (threadIdx.x == 0 && sp > 0.0f) atomicAdd(loss, (logf(sa) - logf(sp)) * inv_g);
+        if (threadIdx.x == 0) {
+            const float l = sp > 0.0f ? (logf(sa) - logf(sp)) * inv_g : 0.0f;
+            if (loss_of)
+                loss_of[g] = l;
+            else if (sp > 0.0f)
+                atomicAdd(loss, l);
+        }
         __syncthreads();
     }
 }
 
-// dZ2[i][j] = dy[i] w3[j] [h2 > 0]; gradients of w3 and b3
-__global__ __launch_bounds__(256) void k_bwd3(const float* P, const float* H2, const float* dy, int64_t n, float* dZ2,
-                                              float* grad) {
-    const int j = threadIdx.x & (H - 1);
-    const int r0 = threadIdx.x >> 7;
-    float gw = 0.0f, gb = 0.0f;
-    for (int64_t i = int64_t(blockIdx.x) * 2 + r0; i < n; i += int64_t(gridDim.x) * 2) {
-        const float h = H2[i * H + j];
-        const float d = dy[i];
-        dZ2[i * H + j] = h > 0.0f ? d * P[kOffW3 + j] : 0.0f;
-        gw += d * h;
-        if (j == 0) gb += d;
+// Backward through layer 3 and the gradients of W2, b2, w3, b3 over a range
+// of rows (blockIdx.y): dZ2[i][j] = dy[i] w3[j] [h2 > 0] for the 16 columns j
+// of strip blockIdx.x, and G[j][k] = sum_i dZ2[i][j] h1[i][k] (rows are the K
+// of the matrix product) into the range's record of ``part`` (kRec floats).
+// Partial records and a second kernel instead of float atomics: every range's
+// 16 k sums would meet the others' at the memory side.
+__global__ __launch_bounds__(kThreads) void k_back2(const float* P, const float* H1, const float* H2, const float* dy,
+                                                    int64_t n, int64_t rows, float* dZ2, float* part) {
+    constexpr int R = 32;             // rows per step
+    constexpr int kRow = H + 16;      // four rows of 16 floats cover the banks
+    __shared__ __align__(16) float si[R][kRow];
+    __shared__ float sd[R][16];
+    __shared__ float red[3][16][17];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, fr = lane & 15, q = lane >> 4;
+    const int j0 = 16 * int(blockIdx.x);
+    const int64_t i0 = rows * blockIdx.y, i1 = i0 + rows < n ? i0 + rows : n;
+    const int c = t & 15, r0 = t >> 4;
+    const float w3 = P[kOffW3 + j0 + c];
+    float gw = 0.0f, gd = 0.0f, gb = 0.0f;
+    v4f acc[2] = {v4f{0, 0, 0, 0}, v4f{0, 0, 0, 0}};
+    // the next step's rows are requested before the current one's products
+    v4f h1v[R * (H / 4) / kThreads];
+    float h2v[R / 16], dyv[R / 16];
+    const auto request = [&](int64_t base) {
+#pragma unroll
+        for (int u = 0; u < R / 16; ++u) {
+            const int64_t i = base + r0 + 16 * u;
+            h2v[u] = i < i1 ? H2[i * H + j0 + c] : 0.0f;
+            dyv[u] = i < i1 ? dy[i] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < R * (H / 4) / kThreads; ++u) {
+            const int64_t i = base + (t + kThreads * u) / (H / 4);
+            h1v[u] = v4f{0, 0, 0, 0};
+            if (i < i1) h1v[u] = *reinterpret_cast<const v4u*>(H1 + i * H + 4 * (t % (H / 4)));
+        }
+    };
+    request(i0);
+    for (int64_t base = i0; base < i1; base += R) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < R / 16; ++u) {
+            const int64_t i = base + r0 + 16 * u;
+            const float h = h2v[u], d = dyv[u];
+            const float dz = h > 0.0f ? d * w3 : 0.0f;
+            if (i < i1) dZ2[i * H + j0 + c] = dz;
+            gw += d * h;
+            gd += d;
+            gb += dz;
+            sd[r0 + 16 * u][c] = dz;
+        }
+#pragma unroll
+        for (int u = 0; u < R * (H / 4) / kThreads; ++u)
+            *reinterpret_cast<v4f*>(&si[(t + kThreads * u) / (H / 4)][4 * (t % (H / 4))]) = h1v[u];
+        request(base + R);
+        __syncthreads();
+#pragma unroll
+        for (int ib = 0; ib < R / 4; ++ib) {
+            const float a = sd[4 * ib + q][fr];
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+                acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, si[4 * ib + q][32 * w + 16 * cb + fr], acc[cb], 0, 0, 0);
+        }
     }
-    atomicAdd(&grad[kOffW3 + j], gw);
-    if (j == 0) atomicAdd(&grad[kOffB3], gb);
+    float* out = part + blockIdx.y * kRec;
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[(j0 + 4 * q + v) * H + 32 * w + 16 * cb + fr] = acc[cb][v];
+    red[0][r0][c] = gb;
+    red[1][r0][c] = gw;
+    red[2][r0][c] = gd;
+    __syncthreads();
+    if (t < 48) {
+        const int which = t >> 4;
+        float s = 0.0f;
+        for (int r = 0; r < 16; ++r) s += red[which][r][c];
+        if (which < 2)
+            out[H * H + which * H + j0 + c] = s;
+        else if (t == 32 && blockIdx.x == 0)
+            out[H * H + 2 * H] = s;
+    }
 }
 
-// parameter gradient of a dense layer: G[j][k] += sum_i D[i][j] In[i][k],
-// Gb[j] += sum_i D[i][j]; K inputs per row (H or F), 64 rows per block
-template <int K>
-__global__ __launch_bounds__(256) void k_wgrad(const float* D, const float* In, int64_t n, float* Gw, float* Gb) {
-    __shared__ float sd[64][H];
-    __shared__ float si[64][K];
-    constexpr int OUT = H * (K + 1);  // weights and bias
-    float acc[(OUT + 255) / 256];
-#pragma unroll
-    for (int q = 0; q < (OUT + 255) / 256; ++q) acc[q] = 0.0f;
-    for (int64_t base = int64_t(blockIdx.x) * 64; base < n; base += int64_t(gridDim.x) * 64) {
+// Sum of the ranges' records (64 entries per work-group, every wave a quarter
+// of the ranges) into out; the last work-group sums the groups' losses, left
+// at loss_of, and then clears that place: the gradients of W1 and b1.
+__global__ __launch_bounds__(256) void k_sum_records(const float* part, int ranges, float* out, float* loss_of,
+                                                     int n_groups, float* loss) {
+    __shared__ float red[4][64];
+    const int lane = int(threadIdx.x) & 63, w = int(threadIdx.x) >> 6;
+    if (blockIdx.x + 1 == gridDim.x) {
+        if (n_groups == 0) return;
+        float s = 0.0f;
+        for (int g = int(threadIdx.x); g < n_groups; g += 256) s += loss_of[g];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (lane == 0) red[w][0] = s;
         __syncthreads();
-        for (int t = threadIdx.x; t < 64 * H; t += blockDim.x) {
-            const int64_t i = base + t / H;
-            sd[t / H][t % H] = i < n ? D[i * H + t % H] : 0.0f;
-        }
-        for (int t = threadIdx.x; t < 64 * K; t += blockDim.x) {
-            const int64_t i = base + t / K;
-            si[t / K][t % K] = i < n ? In[i * K + t % K] : 0.0f;
-        }
+        for (int g = int(threadIdx.x); g < kOffW2; g += 256) loss_of[g] = 0.0f;
+        if (threadIdx.x == 0) *loss = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
+        return;
+    }
+    if (ranges < 2) return;
+    const int e = int(blockIdx.x) * 64 + lane;
+    float s = 0.0f;
+    if (e < kRec) {
+#pragma unroll 8
+        for (int r = w; r < ranges; r += 4) s += part[int64_t(r) * kRec + e];
+    }
+    red[w][lane] = s;
+    __syncthreads();
+    if (w == 0 && e < kRec) out[e] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+}
+
+// Backward through layer 2, dZ1 = dZ2 W2 masked by h1 > 0, and the gradients
+// of W1 and b1 (summed over the work-group's rows, then by atomics)
+template <int RT>
+__global__ __launch_bounds__(kThreads) void k_back1(const float* P, const float* X, const float* H1, const float* dZ2,
+                                                    int64_t n, float* dZ1, float* grad) {
+    __shared__ __align__(16) float t2[16 * RT][kPad];
+    __shared__ float sx[16 * RT][F];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, fr = lane & 15, q = lane >> 4;
+    v4f wf[2][8];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int kb = 0; kb < 8; ++kb)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj)
+                wf[cb][kb][jj] = P[kOffW2 + (16 * kb + 4 * q + jj) * H + 32 * w + 16 * cb + fr];
+    // thread t sums unit k = t % 128: features 0..4 and the bias, or 5..9
+    const int k = t & (H - 1), half = t >> 7;
+    float g[F / 2], gb = 0.0f;
+#pragma unroll
+    for (int f = 0; f < F / 2; ++f) g[f] = 0.0f;
+    const int64_t tiles = (n + 16 * RT - 1) / (16 * RT);
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t base = tile * (16 * RT);
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < (OUT + 255) / 256; ++q) {
-            const int o = threadIdx.x + 256 * q;
-            if (o >= OUT) break;
-            const int j = o / (K + 1), k = o % (K + 1);
-            float a = 0.0f;
-            if (k < K) {
-                for (int r = 0; r < 64; ++r) a += sd[r][j] * si[r][k];
-            } else {
-                for (int r = 0; r < 64; ++r) a += sd[r][j];
+        for (int e = t; e < 16 * RT * (H / 4); e += kThreads) {
+            const int r = e / (H / 4), c = 4 * (e % (H / 4));
+            v4f d = {0, 0, 0, 0};
+            if (base + r < n) d = *reinterpret_cast<const v4u*>(dZ2 + (base + r) * H + c);
+            *reinterpret_cast<v4f*>(&t2[r][c]) = d;
+        }
+        for (int e = t; e < 16 * RT * F; e += kThreads) sx[e / F][e % F] = base + e / F < n ? X[base * F + e] : 0.0f;
+        __syncthreads();
+        v4f acc[RT][2];
+#pragma unroll
+        for (int rb = 0; rb < RT; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = v4f{0, 0, 0, 0};
+        mul_tile<RT>(t2, wf, lane, acc);
+        __syncthreads();  // every wave has read the tile: it takes dZ1
+#pragma unroll
+        for (int rb = 0; rb < RT; ++rb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * rb + 4 * q + v;
+                const int64_t i = base + r;
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    const int col = 32 * w + 16 * cb + fr;
+                    float d = 0.0f;
+                    if (i < n) {
+                        d = H1[i * H + col] > 0.0f ? acc[rb][cb][v] : 0.0f;
+                        dZ1[i * H + col] = d;
+                    }
+                    t2[r][col] = d;
+                }
             }
-            acc[q] += a;
+        __syncthreads();
+#pragma unroll 4
+        for (int r = 0; r < 16 * RT; ++r) {
+            const float d = t2[r][k];
+#pragma unroll
+            for (int f = 0; f < F / 2; ++f) g[f] += d * sx[r][half * (F / 2) + f];
+            gb += d;
         }
     }
+    // through LDS, so that a wave's atomics go to consecutive addresses (one
+    // gradient per lane at stride F took 75 us for the kernel at 13.4 k rows,
+    // mostly these)
+    __syncthreads();
+    float* sg = &t2[0][0];
+    static_assert(kOffW2 <= 16 * kPad, "fits the smallest tile");
 #pragma unroll
-    for (int q = 0; q < (OUT + 255) / 256; ++q) {
-        const int o = threadIdx.x + 256 * q;
-        if (o >= OUT) break;
-        const int j = o / (K + 1), k = o % (K + 1);
-        if (k < K)
-            atomicAdd(&Gw[j * K + k], acc[q]);
-        else
-            atomicAdd(&Gb[j], acc[q]);
-    }
+    for (int f = 0; f < F / 2; ++f) sg[kOffW1 + k * F + half * (F / 2) + f] = g[f];
+    if (half == 0) sg[kOffB1 + k] = gb;
+    __syncthreads();
+    for (int e = t; e < kOffW2; e += kThreads) atomicAdd(&grad[e], sg[e]);
 }
 
 __global__ __launch_bounds__(256) void k_adam(float* P, const float* g, float* m, float* v, int64_t n, float lr,
@@ -211,6 +388,8 @@ __global__ __launch_bounds__(256) void k_adam(float* P, const float* g, float* m
         P[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
     }
 }
+
+constexpr int64_t kManyRows = 4096;
 
 uint32_t blocks_for(int64_t work, int64_t per, uint32_t cap) {
     return uint32_t(std::max<int64_t>(1, std::min<int64_t>((work + per - 1) / per, cap)));
@@ -228,9 +407,11 @@ tn_status tn_mlp_forward(const float* P, const float* X, int64_t n, float* H1, f
     if (!P || n < 0 || (n > 0 && (!X || !H1 || !H2 || !y))) return TN_EINVAL;
     if (n == 0) return TN_OK;
     hipStream_t s = static_cast<hipStream_t>(stream_);
-    hipLaunchKernelGGL(k_fwd1, dim3(blocks_for(n * H, 256, 65535)), dim3(256), 0, s, P, X, n, H1);
-    hipLaunchKernelGGL(k_dense<true>, dim3(blocks_for(n, 32, 4096)), dim3(256), 0, s, P, H1, nullptr, n, H2);
-    hipLaunchKernelGGL(k_fwd3, dim3(blocks_for(n, 4, 65535)), dim3(256), 0, s, P, H2, n, y);
+    // 32-row tiles once they fill the GPU, 16-row tiles below
+    if (n >= kManyRows)
+        hipLaunchKernelGGL(k_forward<2>, dim3(blocks_for(n, 32, 1024)), dim3(kThreads), 0, s, P, X, n, H1, H2, y);
+    else
+        hipLaunchKernelGGL(k_forward<1>, dim3(blocks_for(n, 16, 1024)), dim3(kThreads), 0, s, P, X, n, H1, H2, y);
     return hipGetLastError() == hipSuccess ? TN_OK : TN_EHIP;
 }
 
@@ -240,17 +421,33 @@ tn_status tn_mlp_backward(const float* P, const float* X, const float* H1, const
     if (!P || !grad || !loss || n < 0 || n_groups < 0) return TN_EINVAL;
     if (n > 0 && (!X || !H1 || !H2 || !y || !labels || !groups || !dZ2 || !dZ1 || !dy)) return TN_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream_);
-    hipLaunchKernelGGL(k_fill, dim3(blocks_for(kParams, 256, 1024)), dim3(256), 0, s, grad, int64_t(kParams), 0.0f);
-    hipLaunchKernelGGL(k_fill, dim3(1), dim3(256), 0, s, loss, int64_t(1), 0.0f);
-    if (n == 0 || n_groups == 0) return hipGetLastError() == hipSuccess ? TN_OK : TN_EHIP;
+    if (n == 0 || n_groups == 0) {
+        hipLaunchKernelGGL(k_zero, dim3(1), dim3(256), 0, s, grad, kParams, loss);
+        return hipGetLastError() == hipSuccess ? TN_OK : TN_EHIP;
+    }
+    // the groups' losses go where the gradients of W1 and b1 come later; more
+    // groups than that add up by atomics
+    float* loss_of = n_groups <= kOffW2 ? grad : nullptr;
+    if (!loss_of) hipLaunchKernelGGL(k_zero, dim3(1), dim3(256), 0, s, grad, kOffW2, loss);
     hipLaunchKernelGGL(k_loss, dim3(uint32_t(std::min<int32_t>(n_groups, 65535))), dim3(256), 0, s, y, labels, groups,
-                       n_groups, dy, loss);
-    hipLaunchKernelGGL(k_bwd3, dim3(blocks_for(n, 2, 8192)), dim3(256), 0, s, P, H2, dy, n, dZ2, grad);
-    hipLaunchKernelGGL(k_wgrad<H>, dim3(blocks_for(n, 64, 1024)), dim3(256), 0, s, dZ2, H1, n, grad + kOffW2,
-                       grad + kOffB2);
-    hipLaunchKernelGGL(k_dense<false>, dim3(blocks_for(n, 32, 4096)), dim3(256), 0, s, P, dZ2, H1, n, dZ1);
-    hipLaunchKernelGGL(k_wgrad<F>, dim3(blocks_for(n, 64, 1024)), dim3(256), 0, s, dZ1, X, n, grad + kOffW1,
-                       grad + kOffB1);
+                       n_groups, dy, loss, loss_of);
+    // ranges of rows whose partial gradients fit dZ1 (written after them); one
+    // range writes the gradient itself, also where a caller lets dZ1 share
+    // memory with a buffer that is still read
+    const auto meets = [&](const float* p, int64_t len) { return p < dZ1 + n * H && dZ1 < p + len; };
+    const bool shared = meets(H1, n * H) || meets(H2, n * H) || meets(dZ2, n * H) || meets(dy, n) || meets(X, n * F);
+    const int64_t ranges = shared ? 1 : std::max<int64_t>(1, std::min<int64_t>({n / 128, n * H / kRec, 64}));
+    const int64_t rows = (n + ranges - 1) / ranges;
+    float* part = ranges > 1 ? dZ1 : grad + kOffW2;
+    hipLaunchKernelGGL(k_back2, dim3(H / 16, uint32_t(ranges)), dim3(kThreads), 0, s, P, H1, H2, dy, n, rows, dZ2,
+                       part);
+    if (ranges > 1 || loss_of)
+        hipLaunchKernelGGL(k_sum_records, dim3((kRec + 63) / 64 + 1), dim3(256), 0, s, part, int(ranges),
+                           grad + kOffW2, grad, loss_of ? n_groups : 0, loss);
+    if (n >= kManyRows)
+        hipLaunchKernelGGL(k_back1<2>, dim3(blocks_for(n, 32, 256)), dim3(kThreads), 0, s, P, X, H1, dZ2, n, dZ1, grad);
+    else
+        hipLaunchKernelGGL(k_back1<1>, dim3(blocks_for(n, 16, 256)), dim3(kThreads), 0, s, P, X, H1, dZ2, n, dZ1, grad);
     return hipGetLastError() == hipSuccess ? TN_OK : TN_EHIP;
 }
 

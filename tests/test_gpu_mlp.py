@@ -94,3 +94,50 @@ def test_training_steps_lower_the_loss():
         losses.append(loss.item())
         tn.mlp_adam(P, grad, m, v, t, lr=3e-3)
     assert losses[-1] < 0.5 * losses[0]
+
+
+# row counts around a tile (16 rows, 32 from 4096 rows on), a second range of
+# rows (260) and the switch of tiles
+@pytest.mark.parametrize("n", [15, 16, 17, 33, 259, 260, 263, 4095, 4096, 4131])
+@pytest.mark.parametrize("share", ["none", "dz1=dz2", "dz1=h1"])
+def test_row_tiles_and_shared_buffers(n, share):
+    import torch
+    _say(f"mlp rows n={n} {share}")
+    X, lab, g = _problem(100 + n, n, max(1, n // 40))
+    p = mlp.init_params(n).astype(np.float32)
+    h1, h2, y, grad, dz2, dz1, dy, loss = _buffers(n)
+    P, Xd, Ld, Gd = _dev(p), _dev(X), _dev(lab), _dev(g)
+    tn.mlp_forward(P, Xd, h1, h2, y)
+    torch.cuda.synchronize()
+    p64, x64 = p.astype(np.float64), X.astype(np.float64)
+    # fp32 sums of at most 139 terms: relative to the largest value, well
+    # within 139 2^-24 (the bounds of the test above)
+    want_y, w_h1, w_h2 = mlp.forward(p64, x64)
+    for got, want in ((y, want_y), (h1, w_h1), (h2, w_h2)):
+        assert np.abs(got.cpu().numpy() - want).max() <= 139 * 2.0 ** -24 * max(1.0, np.abs(want).max())
+    out1 = dz2 if share == "dz1=dz2" else h1 if share == "dz1=h1" else dz1
+    tn.mlp_backward(P, Xd, h1, h2, y, Ld, Gd, grad, dz2, out1, dy, loss)
+    torch.cuda.synchronize()
+    want_g = mlp.grad(p64, x64, lab, g)
+    assert loss.item() == pytest.approx(mlp.loss(p64, x64, lab, g), rel=1e-4, abs=1e-5)
+    assert np.allclose(grad.cpu().numpy(), want_g, rtol=2e-3, atol=2e-4 * np.abs(want_g).max())
+
+
+@pytest.mark.parametrize("groups", [1407, 1408, 1409])
+def test_losses_of_many_groups(groups):
+    # up to 1408 groups' losses are kept apart until they are summed, more
+    # are added by atomics
+    import torch
+    n = 3000
+    _say(f"mlp groups={groups}")
+    X, lab, g = _problem(groups, n, groups)
+    p = mlp.init_params(5).astype(np.float32)
+    h1, h2, y, grad, dz2, dz1, dy, loss = _buffers(n)
+    P, Xd, Ld, Gd = _dev(p), _dev(X), _dev(lab), _dev(g)
+    tn.mlp_forward(P, Xd, h1, h2, y)
+    tn.mlp_backward(P, Xd, h1, h2, y, Ld, Gd, grad, dz2, dz1, dy, loss)
+    torch.cuda.synchronize()
+    p64, x64 = p.astype(np.float64), X.astype(np.float64)
+    want_g = mlp.grad(p64, x64, lab, g)
+    assert loss.item() == pytest.approx(mlp.loss(p64, x64, lab, g), rel=1e-4, abs=1e-5)
+    assert np.allclose(grad.cpu().numpy(), want_g, rtol=2e-3, atol=2e-4 * np.abs(want_g).max())
