@@ -133,7 +133,7 @@ typedef struct {
 #define TN_FLAG_GENERIC_ONLY 1   /* use only the generic kernel (testing) */
 #define TN_FLAG_NO_MFMA 2        /* never use the int8 matrix-core kernels */
 #define TN_FLAG_TIMING 4         /* record per-kernel-class device times */
-#define TN_FLAG_NO_GRAPH 8       /* batch: launch waves directly, no hipGraph */
+#define TN_FLAG_NO_GRAPH 8       /* accepted, no effect (batches are launched directly) */
 #define TN_FLAG_WIDE_RNS 16      /* RNS with 16-bit primes even where small moduli suffice */
 
 /* ------------------------------------------------------------------ build
@@ -224,7 +224,7 @@ void tn_plan_free(tn_plan* plan);
 tn_status tn_plan_steps(const tn_plan* plan, int32_t* pairs, int32_t cap, int32_t* n_steps);
 /* Self-check of a plan's memory layouts: TN_OK when no two tensors that are
  * alive at the same time overlap in the arena, both for one-step-at-a-time
- * execution and for execution in waves of equal level; TN_EINVAL otherwise. */
+ * execution and with the small steps fused; TN_EINVAL otherwise. */
 tn_status tn_plan_verify(const tn_plan* plan);
 
 /* --------------------------------------------------------------- contract
@@ -272,8 +272,8 @@ tn_status tn_count(const tn_network* net, const tn_plan* plan, const tn_contract
                    uint32_t* limbs, size_t cap, size_t* n_limbs);
 
 /* Batched counting of n formulas: build and order on host threads, then
- * contract all instances together in waves (one persistent launch per wave,
- * captured in a hipGraph). limbs holds cap_per limbs per instance; n_limbs
+ * contract many instances together (their small steps in common launches,
+ * the chains of larger steps side by side). limbs holds cap_per limbs per instance; n_limbs
  * receives each instance's limb count. The workspace is split into
  * sub-batches that fit. stats (nullable) receives n entries. */
 tn_status tn_count_batch(const tn_formula* fs, int32_t n, tn_order_kind kind, uint64_t seed,

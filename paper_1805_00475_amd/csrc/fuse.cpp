@@ -173,10 +173,10 @@ void build_exec(const Plan& plan, int es, Exec& ex) {
             ex.pinit.push_back(id);
             ex.pinit_off.push_back(uint32_t(loff[size_t(id)]));
         }
+        pg.lds_elems = uint32_t(lds.high);
+        ex.lds_bytes = std::max(ex.lds_bytes, lds_of(pg, es));
         ex.progs.push_back(pg);
         root_step.push_back(r);
-        ex.lds_elems = std::max(ex.lds_elems, uint32_t(lds.high));
-        ex.lds_prog = std::max(ex.lds_prog, pg.prog_bytes);
     }
     ex.pinit_first.push_back(int32_t(ex.pinit.size()));
     // blob: headers, programs, initial entries

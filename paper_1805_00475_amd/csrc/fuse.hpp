@@ -32,7 +32,7 @@ struct FuseProg {
     uint32_t n_steps, n_items, n_levels;
     uint32_t final;                        // 1: the root is the whole network's scalar
     int64_t root_off;                      // global output offset (entries), unless final
-    int64_t pad;
+    uint32_t lds_elems, pad;               // its LDS entries (the program follows them)
 };
 static_assert(sizeof(FuseStep) == 16 && sizeof(FuseProg) == 48, "device layout");
 
@@ -48,7 +48,7 @@ struct Exec {
     std::vector<uint32_t> pinit_off;    // their LDS entries
     uint32_t prog_end = 0;              // bytes of headers and programs
     uint32_t n_entries = 0;             // initial entries of all programs
-    uint32_t lds_elems = 0, lds_prog = 0;  // LDS of the largest program: entries, program bytes
+    uint32_t lds_bytes = 0;             // LDS of the largest program
     std::vector<Step> steps;            // steps outside the programs
     std::vector<int32_t> init_ids;      // initial tensors those read
     std::vector<int64_t> init_off;      // and their offsets (entries)
@@ -56,6 +56,10 @@ struct Exec {
     double prog_entries = 0, prog_macs = 0;  // algorithmic totals of the programs, one plane
 };
 
+// LDS of a program for es-byte entries: its tensors, then the program.
+inline uint32_t lds_of(const FuseProg& pg, int es) {
+    return (pg.lds_elems * uint32_t(es) + 15) / 16 * 16 + pg.prog_bytes;
+}
 // Bytes of the blob.
 int64_t blob_bytes(const Exec& ex, bool wide);
 // Writes the blob (zeroed by the caller) for a network's initial entries.

@@ -33,7 +33,6 @@ struct FuseArgs {
     int64_t stride;      // entries between the planes' arenas
     uint64_t* res;
     uint32_t prog_end;   // blob offset of the initial entries
-    uint32_t lds_prog;   // LDS byte offset of the program
     uint32_t p[kMaxGroup], r2[kMaxGroup], r16[kMaxGroup];
     float pinv[kMaxGroup];
 };
@@ -109,25 +108,26 @@ __device__ __forceinline__ uint64_t dot_lds(const uint64_t* a, const uint64_t* b
     return acc;
 }
 
-// WIDE: the initial entries are 32-bit words to be reduced modulo the
-// plane's modulus (else bytes, valid residues in every plane).
+// Program ``prog`` of a blob in one residue plane (arena: the plane's; res: the
+// plane's result). WIDE: the initial entries are 32-bit words to be reduced
+// modulo the plane's modulus (else bytes, valid residues in every plane).
 template <int E, bool WIDE>
-__global__ __launch_bounds__(kFuseThreads) void k_fused(FuseArgs a) {
+__device__ __forceinline__ void run_program(uint8_t* lds, const uint8_t* blob, uint32_t prog, uint32_t prog_end,
+                                            typename ElemT<E>::T* arena, uint64_t* res, const ModSmall& ms) {
     using T = typename ElemT<E>::T;
-    extern __shared__ __align__(16) uint8_t lds[];
     T* const mem = reinterpret_cast<T*>(lds);
-    const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const FuseProg pg = reinterpret_cast<const FuseProg*>(a.blob)[blockIdx.x];
-    const uint32_t p = a.p[g];
-    const ModP mp{p, a.r2[g]};
-    const ModSmall ms{int32_t(p), a.r2[g], a.r16[g], a.pinv[g]};
+    const FuseProg pg = reinterpret_cast<const FuseProg*>(blob)[prog];
+    const uint32_t p = uint32_t(ms.m);
+    const ModP mp{p, ms.r32};
+    uint8_t* const lprog = lds + (pg.lds_elems * uint32_t(sizeof(T)) + 15) / 16 * 16;
     // the program and the initial tensors into LDS
     {
-        const uint4* src = reinterpret_cast<const uint4*>(a.blob + pg.prog);
-        uint4* dst = reinterpret_cast<uint4*>(lds + a.lds_prog);
+        const uint4* src = reinterpret_cast<const uint4*>(blob + pg.prog);
+        uint4* dst = reinterpret_cast<uint4*>(lprog);
         for (uint32_t i = uint32_t(tid); i < pg.prog_bytes / 16; i += kFuseThreads) dst[i] = src[i];
-        const uint8_t* e0 = a.blob + a.prog_end;
+        const uint8_t* e0 = blob + prog_end;
         for (uint32_t i = uint32_t(tid); i < pg.n_init; i += kFuseThreads) {
             if constexpr (WIDE) {
                 const uint32_t v = reinterpret_cast<const uint32_t*>(e0)[pg.init + i];
@@ -145,8 +145,8 @@ __global__ __launch_bounds__(kFuseThreads) void k_fused(FuseArgs a) {
         }
     }
     __syncthreads();
-    const uint4* steps = reinterpret_cast<const uint4*>(lds + a.lds_prog);
-    const uint32_t* items = reinterpret_cast<const uint32_t*>(lds + a.lds_prog + pg.n_steps * 16);
+    const uint4* steps = reinterpret_cast<const uint4*>(lprog);
+    const uint32_t* items = reinterpret_cast<const uint32_t*>(lprog + pg.n_steps * 16);
     const uint32_t* levels = items + pg.n_items;
     uint32_t i0 = 0;
     for (uint32_t L = 0; L < pg.n_levels; ++L) {
@@ -187,14 +187,34 @@ __global__ __launch_bounds__(kFuseThreads) void k_fused(FuseArgs a) {
                 if (!(mw & (kFuseRoot << 16)))
                     mem[offC + c] = out;
                 else if (pg.final)
-                    a.res[g] = uint64_t(int64_t(out));
+                    *res = uint64_t(int64_t(out));
                 else
-                    (static_cast<T*>(a.arena) + g * a.stride + pg.root_off)[c] = out;
+                    arena[pg.root_off + c] = out;
             }
         }
         i0 = i1;
         __syncthreads();
     }
+}
+
+// One plan: programs over blockIdx.x, residue planes over blockIdx.y.
+template <int E, bool WIDE>
+__global__ __launch_bounds__(kFuseThreads) void k_fused(FuseArgs a) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    const int g = blockIdx.y;
+    const ModSmall ms{int32_t(a.p[g]), a.r2[g], a.r16[g], a.pinv[g]};
+    run_program<E, WIDE>(lds, a.blob, blockIdx.x, a.prog_end,
+                         static_cast<typename ElemT<E>::T*>(a.arena) + g * a.stride, a.res + g, ms);
+}
+
+// Many plans: one (plane, program) pair per work-group.
+template <int E>
+__global__ __launch_bounds__(kFuseThreads) void k_fused_many(const FusePlane* planes, const uint2* work) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    const uint2 wk = work[blockIdx.x];
+    const FusePlane pl = planes[wk.x];
+    const ModSmall ms{int32_t(pl.p), pl.r2, pl.r16, pl.pinv};
+    run_program<E, false>(lds, pl.blob, wk.y, pl.prog_end, static_cast<typename ElemT<E>::T*>(pl.arena), pl.res, ms);
 }
 
 template <int E>
@@ -227,19 +247,30 @@ hipError_t launch_fused(const Exec& ex, int el, const uint32_t* primes, int G, c
     a.stride = arena_elems;
     a.res = res;
     a.prog_end = ex.prog_end;
-    const uint32_t es = uint32_t(elem_size(el));
-    a.lds_prog = (ex.lds_elems * es + 15) / 16 * 16;
     StepArgs m{};
     fill_moduli(m, primes, G);
     std::copy(m.p, m.p + G, a.p);
     std::copy(m.r2, m.r2 + G, a.r2);
     std::copy(m.r16, m.r16 + G, a.r16);
     std::copy(m.pinv, m.pinv + G, a.pinv);
-    const uint32_t lds = a.lds_prog + ex.lds_prog;
+    const uint32_t lds = ex.lds_bytes;
     const dim3 grid(uint32_t(ex.progs.size()), uint32_t(G), 1);
     return el == EL_U64  ? launch_el<EL_U64>(a, wide, grid, lds, stream)
            : el == EL_I8 ? launch_el<EL_I8>(a, wide, grid, lds, stream)
                          : launch_el<EL_U32>(a, wide, grid, lds, stream);
+}
+
+hipError_t launch_fused_many(int el, const FusePlane* planes, const void* work, int64_t n, uint32_t lds,
+                             hipStream_t stream) {
+    const dim3 grid(static_cast<uint32_t>(n));
+    const uint2* w = static_cast<const uint2*>(work);
+    if (el == EL_U64)
+        hipLaunchKernelGGL(k_fused_many<EL_U64>, grid, dim3(kFuseThreads), lds, stream, planes, w);
+    else if (el == EL_I8)
+        hipLaunchKernelGGL(k_fused_many<EL_I8>, grid, dim3(kFuseThreads), lds, stream, planes, w);
+    else
+        hipLaunchKernelGGL(k_fused_many<EL_U32>, grid, dim3(kFuseThreads), lds, stream, planes, w);
+    return hipGetLastError();
 }
 
 hipError_t launch_gather(int el, int G, const char* arena_base, int64_t arena_elems, int64_t off, uint64_t* res,

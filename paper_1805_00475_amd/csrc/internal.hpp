@@ -52,7 +52,6 @@ struct Step {
     uint64_t maskA = 0;
     bool initA = false, initB = false;   // operand lives in the shared init region
     int64_t offA = 0, offB = 0, offC = 0;  // element offsets (init region or arena), plan order
-    int64_t woffA = 0, woffB = 0, woffC = 0;  // the same for execution in waves (by level)
     int32_t level = 0;                   // longest chain of steps feeding this one
 };
 
@@ -70,7 +69,6 @@ struct Plan {
     std::vector<int64_t> init_off;             // per initial tensor, element offset
     int64_t init_elems = 0;                    // size of the init region (elements)
     int64_t arena_elems = 0;                   // arena size for one prime (elements), plan order
-    int64_t warena_elems = 0;                  // arena size when steps run in waves by level
     int32_t root = -1;                         // id of the final scalar
     double cost_us = -1;                       // plan_cost, kept by make_plan (-1: not yet)
     bool sketch = false;                       // merges, cost and stats only (sketch_plan)

@@ -52,6 +52,19 @@ void fill_moduli(StepArgs& a, const uint32_t* primes, int G);
 // roots, to res[plane] (int8 residues sign-extended).
 hipError_t launch_fused(const Exec& ex, int el, const uint32_t* primes, int G, const void* d_blob, bool wide,
                         char* arena_base, int64_t arena_elems, uint64_t* res, hipStream_t stream);
+// One residue plane of one of many plans, in device memory.
+struct FusePlane {
+    const uint8_t* blob;
+    void* arena;
+    uint64_t* res;
+    uint32_t prog_end, p, r2, r16;
+    float pinv;
+    uint32_t pad;
+};
+// Programs of many plans of one element kind: n work-groups, work[i] = (index
+// into planes, program), all in device memory; lds: what the largest needs.
+hipError_t launch_fused_many(int el, const FusePlane* planes, const void* work, int64_t n, uint32_t lds,
+                             hipStream_t stream);
 // res[g] = entry off of plane g
 hipError_t launch_gather(int el, int G, const char* arena_base, int64_t arena_elems, int64_t off, uint64_t* res,
                          hipStream_t stream);

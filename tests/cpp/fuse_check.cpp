@@ -76,7 +76,7 @@ static uint64_t run_steps(const Network& net, const Plan& plan, const Exec& ex, 
     return arena.get(uint64_t(ex.steps.back().offC));
 }
 
-static uint64_t run_exec(const Network& net, const Plan& plan, const Exec& ex, bool wide) {
+static uint64_t run_exec(const Network& net, const Plan& plan, const Exec& ex, bool wide, int es) {
     const int64_t nb = ex.progs.empty() ? 0 : blob_bytes(ex, wide);
     std::vector<uint8_t> blob(size_t(nb), 0);
     Mem arena(size_t(ex.arena_elems));
@@ -86,9 +86,9 @@ static uint64_t run_exec(const Network& net, const Plan& plan, const Exec& ex, b
     for (size_t i = 0; i < ex.progs.size(); ++i) {
         FuseProg pg;
         std::memcpy(&pg, blob.data() + i * sizeof pg, sizeof pg);
-        if (pg.prog % 16 || pg.prog + pg.prog_bytes > ex.prog_end || pg.prog_bytes > ex.lds_prog) die("program bytes");
+        if (pg.prog % 16 || pg.prog + pg.prog_bytes > ex.prog_end || lds_of(pg, es) > ex.lds_bytes) die("program bytes");
         if (int64_t(ex.prog_end) + int64_t(pg.init + pg.n_init) * (wide ? 4 : 1) > nb) die("initial entries");
-        Mem lds(ex.lds_elems);
+        Mem lds(pg.lds_elems);
         const uint8_t* e0 = blob.data() + ex.prog_end;
         for (uint32_t k = 0; k < pg.n_init; ++k)
             lds.put(k, wide ? reinterpret_cast<const uint32_t*>(e0)[pg.init + k] : e0[pg.init + k]);
@@ -169,12 +169,13 @@ int main(int argc, char** argv) {
     build_exec(plan, es, ex);
     plain_exec(plan, plain);
     if (ex.progs.empty()) die("no programs");
-    const uint64_t a = run_exec(net, plan, ex, std::atoi(argv[4]) != 0), b = run_exec(net, plan, plain, false);
+    const uint64_t a = run_exec(net, plan, ex, std::atoi(argv[4]) != 0, es),
+                   b = run_exec(net, plan, plain, false, es);
     size_t fused = 0;
     for (auto& p : ex.progs) fused += p.n_steps;
     if (fused + ex.steps.size() != plan.steps.size()) die("steps lost");
-    std::printf("fused %zu of %zu in %zu programs, lds %u + %u, arena %lld against %lld, blob %lld\n", fused,
-                plan.steps.size(), ex.progs.size(), ex.lds_elems * es, ex.lds_prog, (long long)ex.arena_elems,
+    std::printf("fused %zu of %zu in %zu programs, lds %u, arena %lld against %lld, blob %lld\n", fused,
+                plan.steps.size(), ex.progs.size(), ex.lds_bytes, (long long)ex.arena_elems,
                 (long long)plain.arena_elems, (long long)blob_bytes(ex, false));
     std::printf("%llu\n", (unsigned long long)a);
     if (a != b) die("value");
