@@ -12,22 +12,30 @@
 // Work-group tile WM (xA) x WN (xB) with waves of 16 RA x 16 CB outputs:
 // 8 waves (two per SIMD) on 256 x 256 tiles when both free sides have 8
 // bits, else 256 x 128 or 128 x 128; 4 waves on 256 x 64 or 128 x 64 tiles
-// when B's free side has 6 bits (those steps stream A at the memory rate). K goes in stages of one 64-entry
-// chunk: 64-byte LDS rows, filled straight from global memory
-// (global_load_lds_dwordx4, 16 rows per wave instruction) through four
-// buffers; stage k+4 is requested while stage k is multiplied, and at a
-// tile's last stage (every fragment in registers) the next tile's first
-// four stages. One barrier per stage; after it the wave reads the next
-// stage's fragments while the current stage's MFMAs run.
+// when B's free side has 6 bits (those steps stream A at the memory rate).
 //
-// LDS rows: 4 slots of 16 bytes, slot c of row r stored at slot
-// c ^ ((r / 2) % 4). A 16-byte read is served eight lanes at a time, and
-// eight lanes free of bank conflicts cover 128 distinct bytes modulo 128. A
-// fragment read has eight consecutive lanes on eight consecutive rows at one
-// logical slot: rows of one parity lie 128 bytes apart, and (r / 2) % 4 sends
-// the four rows of each parity to four distinct slots. (Measured on gfx950:
-// 212 B/clk per CU with this map, 124 B/clk with c ^ ((r / 4) % 4), whose
-// eight lanes meet in pairs.)
+// K goes in stages of 128 entries: 128-byte LDS rows, whole lines of memory,
+// filled straight from it (global_load_lds_dwordx4, 8 rows per wave
+// instruction). A stage is two steps of 64 entries; while a step's products
+// run, the wave reads the next step's fragments, and one barrier per stage,
+// before its second step, makes the next stage visible and frees this one's
+// buffers. A has three buffers and B two: B's stage k+2 and A's stage k+3 are
+// requested at that barrier, two and four steps before they are read (A's
+// rows are the ones that come from beyond the L2 most often). At a tile's
+// last step (every fragment in registers) the next tile's first two stages
+// are requested; A's third buffer takes the outputs on their way to memory.
+//
+// With 64-byte stages (four buffers of 32 KiB, the same bytes in flight) the
+// loads bound the kernel: a line left the L1 before its second half was
+// asked for, and one CU took in 19 bytes per clock. 256 x 256 tiles, K = 2^13:
+// 2013 us, 1418 with the loads left out, 1814 now.
+//
+// LDS rows: 8 slots of 16 bytes, slot c of row r stored at slot c ^ (r % 8).
+// A 16-byte read is served eight lanes at a time, and eight lanes free of
+// bank conflicts cover 128 distinct bytes modulo 128: a fragment read has
+// eight consecutive lanes on eight consecutive rows at one logical slot, which
+// the XOR sends to eight distinct slots. (K = 64: 64-byte rows, slot c at
+// c ^ ((r / 2) % 4), rows of one parity lying 128 bytes apart.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -46,47 +54,64 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-constexpr int k8Row = 64;                  // LDS row bytes: one 64-entry chunk
-constexpr int k8Bufs = 4;
-constexpr int k8Flush = (1 << 16) / 64;    // chunks per exact int32 range
+constexpr int k8Flush = (1 << 16) / 128;   // stages per exact int32 range
 constexpr int k8MaxRowBytesLog = 25;       // 127 rows of a stage within 32-bit load offsets
 
-// Output addressing of the epilogue, by the host: C offset bits of the
-// tile-local A indices 16 rb (rb < 8) and v (v < 4) and of the B indices
-// 16 cb (cb < 4). A lane holds four outputs, A indices v = 0..3 (A's two
-// lowest bits) at one B index. mode 0: those are C's two lowest bits, so
-// the four are consecutive bytes; mode 1: C's two lowest bits are A's
-// lowest and B's lowest (either order), so a lane and its neighbour (B
-// indices differing in the lowest bit) swap halves and each stores 4
-// consecutive bytes, the even lane those of v < 2 and the odd lane those of
-// v >= 2; sel are the byte selectors of that swap (even, odd lane); mode 2:
-// single bytes. In modes 0 and 1, C's bits 2 and 3 then belong to lane bits
-// x2 and x3 (B indices' four lowest bits are lane bits 0..3, A indices'
-// bits 2 and 3 lane bits 4 and 5, and in mode 1 lane bit 0 stands for A's
-// bit 1): exchanging those with two bits of the block index leaves 16
-// consecutive bytes of C in each lane (x2 = -1: 4-byte stores).
+// Output addressing of the epilogue, by the host. A lane holds, per 16 x 16
+// block, four outputs: A indices v = 0..3 (A's two lowest bits) at one B
+// index. mode 0: those are C's two lowest bits, so the four are consecutive
+// bytes; mode 1: C's two lowest bits are A's lowest and B's lowest (either
+// order), so a lane and its neighbour (B indices differing in the lowest bit)
+// swap halves and each holds 4 consecutive bytes, the even lane those of v < 2
+// and the odd lane those of v >= 2; sel are the byte selectors of that swap
+// (even, odd lane); mode 2 (both are B's): single bytes, at the C offset bits
+// dA, dV, dB of the tile-local A indices 16 rb and v and of the B indices
+// 16 cb.
+//
+// In modes 0 and 1 (other tiles are launched with the operands exchanged where
+// that gives mode 0) a wave's words go through its part of LDS, a piece of at
+// most 4 KiB at a time, and leave in C's order: consecutive lanes store
+// consecutive 16 bytes wherever C is consecutive (at least 32 bytes, as the
+// wave's tile takes the five lowest bits of either side). A word's place is
+// the XOR of a part per lane bit (sLane), per A block (sRb) and per B block
+// (sCb): the C-ordered index of the piece's bits, with the low four bits of
+// the 16-byte chunk index XORed by a map M of the higher ones chosen so that
+// a wave's 64 words fall into 64 banks. Chunk t 64 + lane is read at
+// 16 lane ^ rM.. ^ rT[t] and stored at C offset bits cLane.. | cT[t].
 struct Mfma8Extra {
+    uint64_t hiA, hiB;  // masks of the tile indices: maskA, maskB less the tile's own bits
     uint64_t dA[8], dV[4], dB[4];
     uint32_t sel[2];
-    int32_t mode, x2, x3;
-    int32_t form;  // 16-byte store variant (store_tile8), 0: none
+    int32_t mode;
+    uint32_t sLane[6], sRb[8], sCb[4], rM[2], rT[4];
+    uint64_t cLane[6], cT[4], cPiece;
 };
 
+// How an exact sum x reaches the reduction: RED_BIAS: the accumulator started
+// at the bits of 1.5 2^23, so that as a float it is 1.5 2^23 + x (K <= 256,
+// |x| <= 256 127^2 < 2^22), RED_PLAIN: as it is (K <= 512, |x| < 2^23), RED_FOLD:
+// folded at 2^16 first (|x| < 2^30).
+enum Reduce { RED_BIAS, RED_PLAIN, RED_FOLD };
+constexpr float kBias = 12582912.0f;          // 1.5 2^23
+constexpr int32_t kBiasBits = 0x4b400000;
+
 // Centred residue of an exact int32 sum modulo m <= 255, returned as the low
-// byte of a word. With FOLD, x = h 2^16 + l becomes y = h (2^16 mod m) + l,
-// |y| < 2^15 (m - 1) + 2^16; else the sum covers K <= 512 and
-// |y| = |x| <= 512 127^2. Either way |y| < 2^23 is exact in single precision.
-// One fma adds y fl(1/m) to 1.5 2^23 and rounds the exact sum once: with
-// |y fl(1/m)| < 2^22 the result lies where floats are spaced 1 apart, so its
-// low 24 bits, read as a signed 24-bit integer, are 2^22 + q, q the nearest
+// byte of a word. With RED_FOLD, x = h 2^16 + l becomes y = h (2^16 mod m) + l
+// = x + h ((2^16 mod m) - 2^16) (one 24-bit multiply-add, modulo 2^32),
+// |y| < 2^15 (m - 1) + 2^16; else y = x. Either way |y| < 2^23 is exact in
+// single precision (RED_BIAS: one subtraction, at half the conversion's
+// cycles). One fma adds y fl(1/m) to 1.5 2^23 and rounds the exact sum once:
+// with |y fl(1/m)| < 2^22 the result lies where floats are spaced 1 apart, so
+// its low 24 bits, read as a signed 24-bit integer, are 2^22 + q, q the nearest
 // integer to y fl(1/m) (ties to even). One 24-bit multiply-add gives
 // y - m (2^22 + q) = r - 2^22 m with r = y - q m, whose low byte is r's since
-// 256 divides 2^22 m. |r| <= 127 for every m in 2..255 (checked over every
-// reachable y), so that byte is r in two's complement.
-template <bool FOLD>
+// 256 divides 2^22 m (and the bias). |r| <= 127 for every m in 2..255 (checked
+// over every reachable y), so that byte is r in two's complement.
+template <int RED>
 __device__ __forceinline__ uint32_t res8(int32_t x, int32_t r16, int32_t negm, float inv) {
-    const int32_t y = FOLD ? (x >> 16) * r16 + (x & 0xffff) : x;
-    const float u = __builtin_fmaf(float(y), inv, 12582912.0f);
+    const int32_t y = RED == RED_FOLD ? __mul24(x >> 16, r16 - 65536) + x : x;
+    const float f = RED == RED_BIAS ? __int_as_float(x) - kBias : float(y);
+    const float u = __builtin_fmaf(f, inv, kBias);
     return uint32_t(__mul24(int32_t(__float_as_uint(u)), negm) + y);
 }
 
@@ -96,139 +121,118 @@ __device__ __forceinline__ uint32_t pack4(uint32_t t0, uint32_t t1, uint32_t t2,
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
-// Exchange lane bit k with the index of a pair of words: afterwards the lane
-// with bit k = t holds in x (y) the word the lane with bit k = 0 (1) held in
-// its word t. P = 4 or 5: lane bit 4 or 5, one permlane swap; P = 0: lane
-// bit k < 4 (run-time), a cross-lane read (ds_bpermute) and selects.
-template <int P>
-__device__ __forceinline__ void lane_swap(uint32_t& x, uint32_t& y, int k, int lane) {
-    if constexpr (P == 4 || P == 5) {
-        const auto r = P == 4 ? __builtin_amdgcn_permlane16_swap(x, y, false, false)
-                              : __builtin_amdgcn_permlane32_swap(x, y, false, false);
-        x = r[0];
-        y = r[1];
-    } else {
-        const bool hi = (lane >> k) & 1;
-        const int send = int(hi ? x : y);
-        const int recv = __builtin_amdgcn_ds_bpermute((lane ^ (1 << k)) << 2, send);
-        x = hi ? uint32_t(recv) : x;
-        y = hi ? y : uint32_t(recv);
-    }
-}
-
 // The lane's word of block (rb, cb) (see Mfma8Extra): four reduced outputs
 // packed; with PAIR, half exchanged with the neighbour lane.
-template <int RA, int CB, bool FOLD, bool PAIR>
+template <int RA, int CB, int RED, bool PAIR>
 __device__ __forceinline__ uint32_t out_word(const v4i (&acc)[RA][CB], int rb, int cb, const ModSmall& ms,
                                              uint32_t sel) {
     const int32_t negm = -int32_t(ms.m);
     const int32_t r16 = int32_t(ms.r16);
     const uint32_t x =
-        pack4(res8<FOLD>(acc[rb][cb][0], r16, negm, ms.inv), res8<FOLD>(acc[rb][cb][1], r16, negm, ms.inv),
-              res8<FOLD>(acc[rb][cb][2], r16, negm, ms.inv), res8<FOLD>(acc[rb][cb][3], r16, negm, ms.inv));
+        pack4(res8<RED>(acc[rb][cb][0], r16, negm, ms.inv), res8<RED>(acc[rb][cb][1], r16, negm, ms.inv),
+              res8<RED>(acc[rb][cb][2], r16, negm, ms.inv), res8<RED>(acc[rb][cb][3], r16, negm, ms.inv));
     if constexpr (!PAIR) return x;
     // the neighbour lane's word (quad permutation 1, 0, 3, 2)
     const uint32_t y = uint32_t(__builtin_amdgcn_mov_dpp(int(x), 0xb1, 0xf, 0xf, false));
     return __builtin_amdgcn_perm(x, y, sel);
 }
 
-// 16-byte stores: blocks b = rb + RA cb in groups of four (block bits 0 and
-// 1) exchange those bits with lane bits x2 and x3 (forms P2, P3 of
-// lane_swap); afterwards word t of a group is C's bytes 4t..4t+3 of the
-// lane's 16.
-template <int RA, int CB, bool FOLD, bool PAIR, int P2, int P3>
-__device__ __forceinline__ void store16(const v4i (&acc)[RA][CB], int8_t* C, uint64_t baseC, const Mfma8Extra& ex,
-                                        const ModSmall& ms, int lane) {
+// Bit deposit of a (uniform) tile index: the loop ends with its highest set bit.
+__device__ __forceinline__ uint64_t pdep_from(uint32_t x, uint64_t mask) {
+    uint64_t r = 0;
+    while (x) {
+        const uint64_t low = mask & (~mask + 1);
+        if (x & 1) r |= low;
+        x >>= 1;
+        mask &= mask - 1;
+    }
+    return r;
+}
+
+// Bytes of LDS a wave's output piece takes, and pieces of its tile.
+template <int RA, int CB>
+struct Piece {
+    static constexpr int N = RA * CB * 256 > 4096 ? 2 : 1;
+    static constexpr int RAP = RA / N;  // A blocks of a piece
+    static constexpr int BYTES = RAP * CB * 256;
+    static constexpr int NT = BYTES / 1024;  // chunks per lane
+};
+
+// Stores a wave's outputs of one tile (modes 0 and 1): base is the C offset of
+// the tile and the wave (uniform), st the wave's LDS piece. LDS accesses of a
+// wave are served in order, so its pieces need no barrier. (Lane parts are
+// formed here, per tile: kept in registers through the K loop they would only
+// add pressure.)
+template <int RA, int CB, int RED, bool PAIR>
+__device__ __forceinline__ void store_staged(const v4i (&acc)[RA][CB], int8_t* C, uint64_t base, const Mfma8Extra& ex,
+                                             const ModSmall& ms, int lane, uint8_t* st) {
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    using Pc = Piece<RA, CB>;
+    __asm__ volatile("" : "+v"(lane));
     // (a select: indexing the argument array per lane would load it from
     // memory, and that load's wait would also wait for every load and store
     // in flight)
     const uint32_t sel = (lane & 1) ? ex.sel[1] : ex.sel[0];
+    uint32_t wl = 0, rl = 16u * uint32_t(lane);
+    uint64_t cl = 0;
 #pragma unroll
-    for (int g = 0; g < RA * CB; g += 4) {
-        uint32_t w[4];
+    for (int k = 0; k < 6; ++k) {
+        const bool on = (lane >> k) & 1;
+        wl ^= on ? ex.sLane[k] : 0u;
+        cl |= on ? ex.cLane[k] : 0ull;
+    }
+    rl ^= (lane & 16) ? ex.rM[0] : 0u;
+    rl ^= (lane & 32) ? ex.rM[1] : 0u;
+    int8_t* const out = C + (base | cl);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) w[t] = out_word<RA, CB, FOLD, PAIR>(acc, (g + t) % RA, (g + t) / RA, ms, sel);
-        lane_swap<P2>(w[0], w[1], ex.x2, lane);
-        lane_swap<P2>(w[2], w[3], ex.x2, lane);
-        lane_swap<P3>(w[0], w[2], ex.x3, lane);
-        lane_swap<P3>(w[1], w[3], ex.x3, lane);
-        uint64_t row = baseC | ex.dA[g % RA];
-        __asm__ volatile("" : "+v"(row));
-        *reinterpret_cast<u4*>(C + (row | ex.dB[g / RA])) = u4{w[0], w[1], w[2], w[3]};
+    for (int h = 0; h < Pc::N; ++h) {
+#pragma unroll
+        for (int rb = 0; rb < Pc::RAP; ++rb) {
+            // (through an empty asm statement: all RAP x CB table
+            // combinations in scalar registers would spill)
+            uint32_t row = wl ^ ex.sRb[rb];
+            __asm__ volatile("" : "+v"(row));
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                *reinterpret_cast<uint32_t*>(st + (row ^ ex.sCb[cb])) =
+                    out_word<RA, CB, RED, PAIR>(acc, h * Pc::RAP + rb, cb, ms, sel);
+        }
+        u4 v[Pc::NT];
+#pragma unroll
+        for (int t = 0; t < Pc::NT; ++t) v[t] = *reinterpret_cast<const u4*>(st + (rl ^ ex.rT[t]));
+#pragma unroll
+        for (int t = 0; t < Pc::NT; ++t) *reinterpret_cast<u4*>(out + ((h ? ex.cPiece : 0ull) | ex.cT[t])) = v[t];
     }
 }
 
 // Store a wave's outputs of one tile: lane (fr, q) holds acc[rb][cb][v] for
-// A index 16 rb + 4 q + v and B index 16 cb + fr (plus the wave's offsets);
-// baseC is the C offset of the lane's first stored byte (tile, wave and lane
-// parts, see Mfma8Extra for the modes; form selects the 16-byte variant).
-// (Row offsets pass through an empty asm statement so that the compiler does
-// not precompute all RA x CB table combinations in scalar registers, which
-// would spill.)
-template <int RA, int CB, bool FOLD>
-__device__ __forceinline__ void store_tile8(const v4i (&acc)[RA][CB], int8_t* C, uint64_t baseC, const Mfma8Extra& ex,
-                                            const ModSmall& ms, int lane) {
-    switch (ex.form) {
-        case 1: return store16<RA, CB, FOLD, false, 4, 5>(acc, C, baseC, ex, ms, lane);
-        case 2: return store16<RA, CB, FOLD, false, 4, 0>(acc, C, baseC, ex, ms, lane);
-        case 3: return store16<RA, CB, FOLD, false, 0, 4>(acc, C, baseC, ex, ms, lane);
-        case 4: return store16<RA, CB, FOLD, false, 0, 0>(acc, C, baseC, ex, ms, lane);
-        case 5: return store16<RA, CB, FOLD, true, 0, 4>(acc, C, baseC, ex, ms, lane);
-        case 6: return store16<RA, CB, FOLD, true, 0, 0>(acc, C, baseC, ex, ms, lane);
-        default: break;
-    }
-    // (a select: indexing the argument array per lane would load it from
-    // memory, and that load's wait would also wait for every load and store
-    // in flight)
-    const uint32_t sel = (lane & 1) ? ex.sel[1] : ex.sel[0];
-    if (ex.mode != 2) {
-#pragma unroll
-        for (int rb = 0; rb < RA; ++rb) {
-            uint64_t row = baseC | ex.dA[rb];
-            __asm__ volatile("" : "+v"(row));
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-                *reinterpret_cast<uint32_t*>(C + (row | ex.dB[cb])) = out_word<RA, CB, FOLD, true>(acc, rb, cb, ms, sel);
-        }
+// A index 16 rb + 4 q + v and B index 16 cb + fr (plus the wave's offsets wr,
+// wc, whose C offset is part of base).
+template <int RA, int CB, int RED>
+__device__ __forceinline__ void store_tile8(const v4i (&acc)[RA][CB], int8_t* C, uint64_t base, const StepArgs& a,
+                                            const Mfma8Extra& ex, const ModSmall& ms, int lane, uint8_t* st) {
+    if (ex.mode == 0) {
+        store_staged<RA, CB, RED, false>(acc, C, base, ex, ms, lane, st);
+    } else if (ex.mode == 1) {
+        store_staged<RA, CB, RED, true>(acc, C, base, ex, ms, lane, st);
     } else {
         const int32_t negm = -int32_t(ms.m);
         const int32_t r16 = int32_t(ms.r16);
+        const uint64_t lo = base | pdep64(uint64_t(4 * (lane >> 4)), a.maskA) | pdep64(uint64_t(lane & 15), a.maskB);
+        // (row offsets pass through an empty asm statement so that the
+        // compiler does not precompute all table combinations in scalar
+        // registers, which would spill)
 #pragma unroll
         for (int rb = 0; rb < RA; ++rb) {
-            uint64_t row = baseC | ex.dA[rb];
+            uint64_t row = lo | ex.dA[rb];
             __asm__ volatile("" : "+v"(row));
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    C[row | ex.dV[v] | ex.dB[cb]] = int8_t(res8<FOLD>(acc[rb][cb][v], r16, negm, ms.inv));
+                    C[row | ex.dV[v] | ex.dB[cb]] = int8_t(res8<RED>(acc[rb][cb][v], r16, negm, ms.inv));
         }
     }
-}
-
-// Lane part of the C offset of the lane's first stored byte (see Mfma8Extra):
-// A index wr + 4 q, B index wc + fr; in mode 1 the lane stores the outputs of
-// B index wc + (fr & ~1) and A indices wr + 4 q + 2 (fr & 1) + {0, 1}; with
-// 16-byte stores lane bits x2 and x3 stand for block bits 0 and 1 instead
-// (rb's bit 0, and rb's bit 1 or, with RA = 2, cb's bit 0).
-template <int RA>
-__device__ __forceinline__ uint64_t lane_offset8(const StepArgs& a, const Mfma8Extra& ex, int wr, int wc, int lane) {
-    uint32_t ai = uint32_t(wr), bi = uint32_t(wc);
-    for (int k = 0; k < 6; ++k) {
-        if (!((lane >> k) & 1)) continue;
-        if (ex.mode != 2 && k == ex.x2)
-            ai += 16;
-        else if (ex.mode != 2 && k == ex.x3)
-            (RA >= 4 ? ai : bi) += RA >= 4 ? 32 : 16;
-        else if (k >= 4)
-            ai += 4u << (k - 4);
-        else if (k == 0 && ex.mode == 1)
-            ai += 2;
-        else
-            bi += 1u << k;
-    }
-    return pdep64(ai, a.maskA) | pdep64(bi, a.maskB);
 }
 
 constexpr int lg2(int x) { return x <= 1 ? 0 : 1 + lg2(x / 2); }
@@ -238,13 +242,8 @@ template <int WM_, int WN_, int NW_, int RA_, int CB_>
 struct Cfg {
     static constexpr int WM = WM_, WN = WN_, NW = NW_, RA = RA_, CB = CB_;
     static constexpr int THREADS = 64 * NW;
-    static constexpr int ROWS = WM + WN;
-    static constexpr int BUF = ROWS * k8Row;      // one stage
-    static constexpr int GROUP = 16 * NW;         // stage rows per load instruction of all waves
-    static constexpr int LOADS = ROWS / GROUP;    // load instructions per wave and stage
     static constexpr int WAVES_A = WM / (16 * RA);
     static constexpr int LGM = lg2(WM), LGN = lg2(WN);
-    static_assert(WM % GROUP == 0 && WN % GROUP == 0, "a load instruction covers A rows or B rows only");
     static_assert(WAVES_A * (WN / (16 * CB)) == NW, "waves cover the tile");
 };
 using Cfg256x256 = Cfg<256, 256, 8, 8, 4>;
@@ -253,183 +252,238 @@ using Cfg128x128 = Cfg<128, 128, 8, 4, 2>;
 using Cfg256x64 = Cfg<256, 64, 4, 4, 4>;
 using Cfg128x64 = Cfg<128, 64, 4, 2, 4>;
 
-// One step on int8 residues: tiles of WM x WN outputs dealt round-robin to
-// the work-groups, K split over blockIdx.y into `splits` ranges (partial
-// residues to `part` when splits > 1), residue planes over blockIdx.z.
-// NK: 1 or 2 stages per tile and block row, or 4 for any power of two >= 4.
-// FOLD: the sums exceed 8 stages, so the epilogue folds them at 2^16 first.
-template <class G, int NK, bool FOLD>
-__global__ __launch_bounds__(G::THREADS, 1) void k_mfma8(StepArgs a, Mfma8Extra ex, int splits, int8_t* part,
-                                                         int64_t part_stride) {
+// One step on int8 residues: the tiles of WM x WN outputs of all residue planes
+// are dealt round-robin to a grid that fills the GPU once, K split over
+// blockIdx.y into `splits` ranges (partial residues to `part` when splits > 1).
+// NST: stages of 128 entries per tile and block row: 1, 2, or 4 for any power
+// of two >= 4; 0: K = 64.
+//
+// Loads and stores share one completion counter and complete in order. The
+// next tile's first stages are requested before the epilogue's stores (STORES
+// per lane), so the waits of its first stage leave that many operations
+// outstanding on top; waiting for the stores themselves to reach memory would
+// hold every tile up.
+template <class G, int NST, int RED>
+__global__ __launch_bounds__(G::THREADS, 1) void k_mfma8(StepArgs a, Mfma8Extra ex, int planes, int splits,
+                                                         int8_t* part, int64_t part_stride) {
     constexpr int RA = G::RA, CB = G::CB;
-    // one LDS buffer per stage in flight: tiles of one or two stages leave
-    // room for more work-groups per CU
-    constexpr int NBUF = NK < k8Bufs ? NK : k8Bufs;
-    __shared__ __align__(1024) uint8_t lds[NBUF * G::BUF + G::THREADS * 8];
-    uint64_t* const lconst = reinterpret_cast<uint64_t*>(lds + NBUF * G::BUF);
+    using Pc = Piece<RA, CB>;
+    constexpr int STORES = Pc::N * Pc::NT;
+    constexpr int ROW = NST ? 128 : 64;               // LDS row bytes
+    constexpr int RPI = 1024 / ROW;                   // rows per load instruction
+    constexpr int LA = G::WM / (RPI * G::NW), LB = G::WN / (RPI * G::NW);  // loads per wave and stage
+    static_assert(LA * RPI * G::NW == G::WM && LB * RPI * G::NW == G::WN, "whole load instructions");
+    constexpr int BUFA = G::WM * ROW, BUFB = G::WN * ROW;
+    // A's buffers (the last one takes the outputs) and B's
+    constexpr int NA = NST >= 2 ? 3 : 2, NB = NST >= 2 ? 2 : 1;
+    constexpr int OUTB = G::NW * Pc::BYTES;           // output pieces of the waves
+    constexpr int LASTA = OUTB > BUFA ? OUTB : BUFA;
+    // (one array for everything: with two, the compiler waits for every load
+    // into LDS in flight before each fragment read)
+    __shared__ __align__(1024) uint8_t lds[NB * BUFB + (NA - 1) * BUFA + LASTA];
+    uint8_t* const ldsA = lds + NB * BUFB;
 
-    const int g = blockIdx.z;
-    const int8_t* A = static_cast<const int8_t*>(a.A) + g * a.strideA;
-    const int8_t* B = static_cast<const int8_t*>(a.B) + g * a.strideB;
-    int8_t* C = static_cast<int8_t*>(a.C) + g * a.strideC;
-    const ModSmall ms{int32_t(a.p[g]), a.r2[g], a.r16[g], a.pinv[g]};
-
+    const int8_t* const A = static_cast<const int8_t*>(a.A);
+    const int8_t* const B = static_cast<const int8_t*>(a.B);
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = (w % G::WAVES_A) * 16 * RA, wc = (w / G::WAVES_A) * 16 * CB;
     const uint64_t rowBytes = uint64_t(1) << a.s;
-    const int nk = NK >= 4 ? (1 << (a.s - 6)) / splits : NK;  // stages per tile and block row
-    const int kc0 = int(blockIdx.y) * nk;
+    const int nst = NST >= 4 ? (1 << (a.s - 7)) / splits : NST;  // stages per tile and block row
+    const uint64_t k0 = uint64_t(blockIdx.y) * uint64_t(nst) * 128;
     const int lgA = a.fA - G::LGM, lgB = a.fB - G::LGN;
     const uint32_t T = 1u << (lgA + lgB);
-    if (blockIdx.x >= T) return;
+    const uint64_t total = uint64_t(T) * uint64_t(planes);
+    if (blockIdx.x >= total) return;
+    // outputs leave through the staged stores, STORES per lane and tile
+    const bool staged = splits == 1 && ex.mode != 2;
 
     const int fr = lane & 15, q = lane >> 4;
-    // lane part of the output offset, kept in LDS: the epilogue reads it
-    // once per tile, and in registers through the K loop it would only add
-    // pressure
-    lconst[tid] = lane_offset8<RA>(a, ex, wr, wc, lane);
-    // loads: lane l of wave w, instruction i fills physical slot l % 4 of
-    // stage row r = GROUP i + 16 w + l / 4, i.e. logical slot
-    // (l % 4) ^ ((r / 2) % 4) = (l % 4) ^ ((l / 8) % 4): bytes 16 of that
-    // slot of the row's chunk
+    const uint64_t waveC = pdep64(uint64_t(wr), a.maskA) | pdep64(uint64_t(wc), a.maskB);
+    uint8_t* const wstage = ldsA + (NA - 1) * BUFA + w * Pc::BYTES;
+    // loads: lane l of wave w, instruction i fills physical slot l % 8 (4) of
+    // stage row r = RPI (NW i + w) + l / 8 (4), i.e. logical slot
+    // (l % 8) ^ (r % 8) ((l % 4) ^ ((r / 2) % 4)): 16 bytes of the row
     const uint32_t voff =
-        uint32_t(16 * w + (lane >> 2)) * uint32_t(rowBytes) + 16u * uint32_t((lane & 3) ^ ((lane >> 3) & 3));
-    // fragment reads: row wr + fr (A) or WM + wc + fr (B) of a stage, at
-    // logical slot q
-    const int sw = 16 * (q ^ ((fr >> 1) & 3));
-    const uint32_t rdA = uint32_t((wr + fr) * k8Row + sw), rdB = uint32_t((G::WM + wc + fr) * k8Row + sw);
-    __syncthreads();
+        NST ? uint32_t(8 * w + (lane >> 3)) * uint32_t(rowBytes) + 16u * uint32_t((lane & 7) ^ (lane >> 3))
+            : uint32_t(16 * w + (lane >> 2)) * uint32_t(rowBytes) + 16u * uint32_t((lane & 3) ^ ((lane >> 3) & 3));
+    // fragment reads: row wr + fr of A's buffer, wc + fr of B's, at logical
+    // slot q of the stage's first step (its second: physical slot ^ 4)
+    const int sw = NST ? 16 * (q ^ (fr & 7)) : 16 * (q ^ ((fr >> 1) & 3));
+    const uint32_t rdA = uint32_t((wr + fr) * ROW + sw), rdB = uint32_t((wc + fr) * ROW + sw);
 
     // The per-lane offsets pass through empty asm statements where they are
     // used, so that addresses are formed there from uniform bases (kept in
     // scalar registers) instead of being kept per lane across the loop.
-    auto fetch = [&](const int8_t* tA, const int8_t* tB, int chunk, int buf) {
+    auto fetch = [&](const int8_t* t, int stage, uint8_t* dst, auto n) {
         uint32_t vo = voff;
         __asm__ volatile("" : "+v"(vo));
-        const uint64_t co = uint64_t(chunk) * 64;
+        const int8_t* base = t + (k0 + uint64_t(stage) * 128);
 #pragma unroll
-        for (int i = 0; i < G::LOADS; ++i) {
-            const int r0 = G::GROUP * i;  // first stage row of instruction i (all A or all B)
-            const int8_t* base = (r0 < G::WM ? tA + uint64_t(r0) * rowBytes : tB + uint64_t(r0 - G::WM) * rowBytes) + co;
-            __builtin_amdgcn_global_load_lds(base + vo, (lds_ptr_t)(lds + buf * G::BUF + w * 1024 + i * (G::NW * 1024)),
-                                             16, 0, 0);
-        }
+        for (int i = 0; i < decltype(n)::value; ++i)
+            __builtin_amdgcn_global_load_lds(base + uint64_t(RPI * G::NW * i) * rowBytes + vo,
+                                             (lds_ptr_t)(dst + w * 1024 + i * (G::NW * 1024)), 16, 0, 0);
     };
+    using nA = std::integral_constant<int, LA>;
+    using nB = std::integral_constant<int, LB>;
     v4i fa[RA], b0[CB], b1[CB];
-    auto read_stage_b = [&](int buf, v4i(&b)[CB]) {
-        uint32_t o = rdB;
+    auto lane_at = [&](uint32_t o, int flip) {
         __asm__ volatile("" : "+v"(o));
-        const uint8_t* p = lds + o + buf * G::BUF;
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) b[cb] = *reinterpret_cast<const v4i*>(p + cb * 16 * k8Row);
+        return o ^ uint32_t(flip);
     };
-    auto a_row = [&](int buf) {
-        uint32_t o = rdA;
-        __asm__ volatile("" : "+v"(o));
-        return lds + o + buf * G::BUF;
+    auto read_b = [&](const uint8_t* p, v4i(&b)[CB]) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) b[cb] = *reinterpret_cast<const v4i*>(p + cb * 16 * ROW);
     };
 
-    uint32_t tile = blockIdx.x, ta, tb;
-    tile_coords_lg(tile, lgA, lgB, ta, tb);
-    const int8_t* tA = A + uint64_t(ta) * G::WM * rowBytes;
-    const int8_t* tB = B + uint64_t(tb) * G::WN * rowBytes;
-#pragma unroll
-    for (int c = 0; c < NBUF; ++c) fetch(tA, tB, kc0 + c, c);
+    // tile L of plane g = L / T: its coordinates and first rows
+    const auto locate = [&](uint64_t L, uint32_t& g, uint32_t& ta, uint32_t& tb, const int8_t*& pA, const int8_t*& pB) {
+        g = uint32_t(L >> (lgA + lgB));
+        tile_coords_lg(uint32_t(L) & (T - 1), lgA, lgB, ta, tb);
+        pA = A + g * a.strideA + uint64_t(ta) * G::WM * rowBytes;
+        pB = B + g * a.strideB + uint64_t(tb) * G::WN * rowBytes;
+    };
+    // a tile's first stage, and its second
+    const auto fetch_first = [&](const int8_t* pA, const int8_t* pB) {
+        fetch(pA, 0, ldsA, nA());
+        fetch(pB, 0, lds, nB());
+        if constexpr (NST >= 2) {
+            fetch(pA, 1, ldsA + BUFA, nA());
+            fetch(pB, 1, lds + BUFB, nB());
+        }
+    };
+    uint64_t L = blockIdx.x;
+    uint32_t g, ta, tb;
+    const int8_t *tA, *tB;
+    locate(L, g, ta, tb, tA, tB);
+    fetch_first(tA, tB);
+    // (the first tile follows no stores)
+    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
 
     for (;;) {
         v4i acc[RA][CB];
-#pragma unroll
-        for (int i = 0; i < RA; ++i)
-#pragma unroll
-            for (int j = 0; j < CB; ++j) acc[i][j] = v4i{0, 0, 0, 0};
-        // every load and store of the wave has completed (loads and stores
-        // share one counter); stage 0 is visible to all waves. A fragments:
-        // one set, each refilled with the next stage's as soon as its last
-        // product of the stage is issued; B fragments: two sets
-        chunk_barrier<0>();
+        // stage 0 has landed and is visible to all waves. A fragments: one set,
+        // each refilled with the next step's as soon as its last product of
+        // the step is issued; B fragments: two sets
+        if (staged)
+            chunk_barrier<(NST >= 2 ? LA + LB : 0) + STORES>();
+        else
+            chunk_barrier<0>();
         {
-            const uint8_t* pa = a_row(0);
+            const uint8_t* pa = ldsA + lane_at(rdA, 0);
 #pragma unroll
-            for (int rb = 0; rb < RA; ++rb) fa[rb] = *reinterpret_cast<const v4i*>(pa + rb * 16 * k8Row);
+            for (int rb = 0; rb < RA; ++rb) fa[rb] = *reinterpret_cast<const v4i*>(pa + rb * 16 * ROW);
+            read_b(lds + lane_at(rdB, 0), b0);
         }
-        read_stage_b(0, b0);
 
-        const uint32_t next = tile + gridDim.x;
-        const bool more = next < T;
-        uint32_t nta = 0, ntb = 0;
-        if (more) tile_coords_lg(next, lgA, lgB, nta, ntb);
-        const int8_t* nA = A + uint64_t(nta) * G::WM * rowBytes;
-        const int8_t* nB = B + uint64_t(ntb) * G::WN * rowBytes;
-        // Stage kc from fa and bc. Other than the tile's last stage (LAST),
-        // a step first waits until stage kc + 1 has landed with at most VM
-        // loads (stages kc + 2, kc + 3) still in flight, so that no wave reads
-        // stage kc any more; with FETCH its buffer then takes stage kc + 4;
-        // stage kc + 1 is read into fa and bn.
-        auto step = [&](int kc, v4i(&bc)[CB], v4i(&bn)[CB], auto vm, auto fetch_next, auto last) {
-            constexpr int VM = decltype(vm)::value;
-            constexpr bool FETCH = decltype(fetch_next)::value, LAST = decltype(last)::value;
-            const uint8_t* pa = nullptr;
-            if constexpr (!LAST) {
-                chunk_barrier<VM>();
-                if constexpr (FETCH) fetch(tA, tB, kc0 + kc + 4, kc & 3);
+        const uint64_t next = L + gridDim.x;
+        const bool more = next < total;
+        uint32_t ng = 0, nta = 0, ntb = 0;
+        const int8_t *nxA = A, *nxB = B;
+        if (more) locate(next, ng, nta, ntb, nxA, nxB);
+        // The products of one step from fa and bc (START: the tile's first, onto
+        // the bias or zero); meanwhile, with READ, the next step's fragments
+        // from pa and pb into fa and bn.
+        auto products = [&](v4i(&bc)[CB], v4i(&bn)[CB], const uint8_t* pa, const uint8_t* pb, auto read, auto start) {
+            constexpr bool READ = decltype(read)::value, START = decltype(start)::value;
+            constexpr int32_t Z = RED == RED_BIAS ? kBiasBits : 0;
+            if constexpr (READ) {
                 // (the compiler would otherwise wait at the MFMAs for the
-                // fragment reads below, to order them after the loads above)
+                // fragment reads below, to order them after loads in flight)
                 __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(63));
-                read_stage_b((kc + 1) & 3, bn);
-                pa = a_row((kc + 1) & 3);
-            } else {
-                // every fragment of the tile is in registers, so the four
-                // buffers take the next tile's first stages
-                chunk_barrier<63>();
-                if (more)
-#pragma unroll
-                    for (int c = 0; c < NBUF; ++c) fetch(nA, nB, kc0 + c, c);
+                read_b(pb, bn);
             }
 #pragma unroll
             for (int rb = 0; rb < RA; ++rb) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
-                    acc[rb][cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[rb], bc[cb], acc[rb][cb], 0, 0, 0);
-                if constexpr (!LAST) fa[rb] = *reinterpret_cast<const v4i*>(pa + rb * 16 * k8Row);
+                    acc[rb][cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                        fa[rb], bc[cb], START ? v4i{Z, Z, Z, Z} : acc[rb][cb], 0, 0, 0);
+                if constexpr (READ) fa[rb] = *reinterpret_cast<const v4i*>(pa + rb * 16 * ROW);
             }
         };
         using yes = std::true_type;
         using no = std::false_type;
-        using vm2 = std::integral_constant<int, 2 * G::LOADS>;
-        using vm1 = std::integral_constant<int, G::LOADS>;
-        using vm0 = std::integral_constant<int, 0>;
-        // Main loop: every step waits for the same count and fetches. The
-        // sums stay exact in int32 for k8Flush stages; after each full range
-        // they are reduced to centred residues (the last range ends in the
-        // epilogue).
-        int kc = 0;
-        while (NK >= 4 && kc + 4 < nk) {
-            const int end = std::min(nk - 4, kc + k8Flush);
-            for (; kc < end; kc += 2) {
-                step(kc, b0, b1, vm2(), yes(), no());
-                step(kc + 1, b1, b0, vm2(), yes(), no());
-            }
-            if (kc < nk - 4) {
-#pragma unroll
-                for (int i = 0; i < RA; ++i)
-#pragma unroll
-                    for (int j = 0; j < CB; ++j)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[i][j][v] = ms.center32(acc[i][j][v]);
-            }
-        }
-        // the last stages
-        if constexpr (NK >= 4) {
-            step(nk - 4, b0, b1, vm2(), no(), no());
-            step(nk - 3, b1, b0, vm1(), no(), no());
-            step(nk - 2, b0, b1, vm0(), no(), no());
-            step(nk - 1, b1, b0, vm0(), no(), yes());
-        } else if constexpr (NK == 2) {
-            step(0, b0, b1, vm0(), no(), no());
-            step(1, b1, b0, vm0(), no(), yes());
+        // first step of a stage in A buffer sa, B buffer sb
+        auto first = [&](int sa, int sb, auto start) {
+            products(b0, b1, ldsA + sa * BUFA + lane_at(rdA, 64), lds + sb * BUFB + lane_at(rdB, 64), yes(), start);
+        };
+        // its second step; the next stage is in A buffer na, B buffer nb
+        auto second = [&](int na, int nb) {
+            products(b1, b0, ldsA + na * BUFA + lane_at(rdA, 0), lds + nb * BUFB + lane_at(rdB, 0), yes(), no());
+        };
+        // the tile's last step: every fragment is in registers, so the
+        // buffers take the next tile's first stages
+        auto last = [&](v4i(&bc)[CB], v4i(&bn)[CB], auto start) {
+            chunk_barrier<63>();
+            if (more) fetch_first(nxA, nxB);
+            products(bc, bn, nullptr, nullptr, no(), start);
+        };
+        const ModSmall ms{int32_t(a.p[g]), a.r2[g], a.r16[g], a.pinv[g]};
+        // the tile's C offset, formed while the first products run
+        uint64_t baseC = 0;
+        const auto place = [&]() { baseC = (pdep_from(ta, ex.hiA) | pdep_from(tb, ex.hiB)) | waveC; };
+        if constexpr (NST == 0) {
+            last(b0, b1, yes());
+            place();
+        } else if constexpr (NST == 1) {
+            first(0, 0, yes());
+            place();
+            last(b1, b0, no());
+        } else if constexpr (NST == 2) {
+            first(0, 0, yes());
+            place();
+            chunk_barrier<STORES>();  // stage 1 has landed (younger: the last tile's stores)
+            second(1, 1);
+            first(1, 1, no());
+            last(b1, b0, no());
         } else {
-            step(0, b0, b1, vm0(), no(), yes());
+            first(0, 0, yes());
+            place();
+            chunk_barrier<STORES>();
+            fetch(tA, 2, ldsA + 2 * BUFA, nA());
+            fetch(tB, 2, lds, nB());
+            fetch(tA, 3, ldsA, nA());
+            second(1, 1);
+            // Stage st, in A buffer sa: the barrier waits for stage st + 1
+            // (younger: A's stage st + 2). The sums stay exact in int32 for
+            // k8Flush stages; after each full range they are reduced to
+            // centred residues (the last range ends in the epilogue).
+            int st = 1, sa = 1, range = k8Flush;
+            while (st + 3 < nst) {
+                const int end = std::min(nst - 3, range);
+                for (; st < end; ++st) {
+                    const int na = sa == 2 ? 0 : sa + 1, sb = st & 1;
+                    first(sa, sb, no());
+                    chunk_barrier<LA>();
+                    fetch(tB, st + 2, lds + sb * BUFB, nB());
+                    fetch(tA, st + 3, ldsA + sa * BUFA, nA());
+                    second(na, sb ^ 1);
+                    sa = na;
+                }
+                range += k8Flush;
+                if (st + 3 < nst) {
+#pragma unroll
+                    for (int i = 0; i < RA; ++i)
+#pragma unroll
+                        for (int j = 0; j < CB; ++j)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) acc[i][j][v] = ms.center32(acc[i][j][v]);
+                }
+            }
+            // the last three stages (st = nst - 3 is odd)
+            int na = sa == 2 ? 0 : sa + 1;
+            first(sa, 1, no());
+            chunk_barrier<LA>();
+            fetch(tB, nst - 1, lds + BUFB, nB());
+            second(na, 0);
+            sa = na;
+            na = sa == 2 ? 0 : sa + 1;
+            first(sa, 0, no());
+            chunk_barrier<0>();
+            second(na, 1);
+            first(na, 1, no());
+            last(b1, b0, no());
         }
 
         // epilogue: lane holds A index wr + 16 rb + 4 q + v, B index
@@ -437,13 +491,14 @@ __global__ __launch_bounds__(G::THREADS, 1) void k_mfma8(StepArgs a, Mfma8Extra 
         const int32_t negm = -int32_t(ms.m);
         const int32_t r16 = int32_t(ms.r16);
         auto packed = [&](int rb, int cb) {
-            return pack4(res8<FOLD>(acc[rb][cb][0], r16, negm, ms.inv), res8<FOLD>(acc[rb][cb][1], r16, negm, ms.inv),
-                         res8<FOLD>(acc[rb][cb][2], r16, negm, ms.inv), res8<FOLD>(acc[rb][cb][3], r16, negm, ms.inv));
+            return pack4(res8<RED>(acc[rb][cb][0], r16, negm, ms.inv), res8<RED>(acc[rb][cb][1], r16, negm, ms.inv),
+                         res8<RED>(acc[rb][cb][2], r16, negm, ms.inv), res8<RED>(acc[rb][cb][3], r16, negm, ms.inv));
         };
         if (splits > 1) {
             // partial residues of this K range, tile-local order (j, i): the
             // lane's four A indices are consecutive bytes
-            int8_t* pt = part + blockIdx.z * part_stride + (uint64_t(blockIdx.y) * T + tile) * (G::WM * G::WN);
+            int8_t* pt =
+                part + g * part_stride + (uint64_t(blockIdx.y) * T + (uint32_t(L) & (T - 1))) * (G::WM * G::WN);
             uint32_t lo = uint32_t((wc + fr) * G::WM + wr + 4 * q);
             __asm__ volatile("" : "+v"(lo));
 #pragma unroll
@@ -452,18 +507,15 @@ __global__ __launch_bounds__(G::THREADS, 1) void k_mfma8(StepArgs a, Mfma8Extra 
                 for (int cb = 0; cb < CB; ++cb)
                     *reinterpret_cast<uint32_t*>(pt + lo + uint32_t(16 * cb * G::WM + 16 * rb)) = packed(rb, cb);
         } else {
-            int ci = tid;
-            __asm__ volatile("" : "+v"(ci));  // read here, per tile
-            const uint64_t baseC =
-                (pdep64(uint64_t(ta) * G::WM, a.maskA) | pdep64(uint64_t(tb) * G::WN, a.maskB)) | lconst[ci];
-            store_tile8<RA, CB, FOLD>(acc, C, baseC, ex, ms, lane);
+            store_tile8<RA, CB, RED>(acc, static_cast<int8_t*>(a.C) + g * a.strideC, baseC, a, ex, ms, lane, wstage);
         }
         if (!more) break;
-        tile = next;
+        L = next;
+        g = ng;
         ta = nta;
         tb = ntb;
-        tA = nA;
-        tB = nB;
+        tA = nxA;
+        tB = nxB;
     }
 }
 
@@ -504,6 +556,7 @@ __global__ __launch_bounds__(256) void k_mfma8_reduce(StepArgs a, const int8_t* 
 template <class G, int S, int U = 1>
 __global__ __launch_bounds__(G::THREADS) void k_mfma8_short(StepArgs a, Mfma8Extra ex) {
     constexpr int RA = G::RA, CB = G::CB, K = 1 << S;
+    __shared__ __align__(1024) uint8_t stage[G::NW * Piece<RA, CB>::BYTES];
     const int g = blockIdx.z;
     const int8_t* A = static_cast<const int8_t*>(a.A) + g * a.strideA;
     const int8_t* B = static_cast<const int8_t*>(a.B) + g * a.strideB;
@@ -515,7 +568,8 @@ __global__ __launch_bounds__(G::THREADS) void k_mfma8_short(StepArgs a, Mfma8Ext
     const int lgA = a.fA - G::LGM, lgB = a.fB - G::LGN;
     const uint32_t T = 1u << (lgA + lgB);
     const int fr = lane & 15, q = lane >> 4;
-    const uint64_t lc = lane_offset8<RA>(a, ex, wr, wc, lane);
+    const uint64_t waveC = pdep64(uint64_t(wr), a.maskA) | pdep64(uint64_t(wc), a.maskB);
+    uint8_t* const wstage = stage + w * Piece<RA, CB>::BYTES;
     // lane's fragment offset within a tile's rows: row wr + fr (A) or
     // wc + fr (B), K offset 8 q
     const uint32_t offA = uint32_t((wr + fr) * K + 8 * q), offB = uint32_t((wc + fr) * K + 8 * q);
@@ -558,13 +612,14 @@ __global__ __launch_bounds__(G::THREADS) void k_mfma8_short(StepArgs a, Mfma8Ext
             for (int rb = 0; rb < RA; ++rb)
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
-                    acc[rb][cb] = __builtin_amdgcn_mfma_i32_16x16x32_i8(fa[u][rb], fb[u][cb], v4i{0, 0, 0, 0}, 0, 0, 0);
+                    acc[rb][cb] = __builtin_amdgcn_mfma_i32_16x16x32_i8(
+                        fa[u][rb], fb[u][cb], v4i{kBiasBits, kBiasBits, kBiasBits, kBiasBits}, 0, 0, 0);
             const uint32_t next = t + U * stride;
             if (next < T) fetch(next, u);
             uint32_t ta, tb;
             tile_coords_lg(t, lgA, lgB, ta, tb);
-            const uint64_t baseC = (pdep64(uint64_t(ta) * G::WM, a.maskA) | pdep64(uint64_t(tb) * G::WN, a.maskB)) | lc;
-            store_tile8<RA, CB, false>(acc, C, baseC, ex, ms, lane);
+            const uint64_t baseC = (pdep_from(ta, ex.hiA) | pdep_from(tb, ex.hiB)) | waveC;
+            store_tile8<RA, CB, RED_BIAS>(acc, C, baseC, a, ex, ms, lane, wstage);
         }
         tile += U * stride;
         if (tile >= T) break;
@@ -578,8 +633,14 @@ uint64_t pdep_host(uint64_t x, uint64_t m) {
     return r;
 }
 
+template <class Gm>
 Mfma8Extra extra_of(const StepArgs& a) {
+    using Pc = Piece<Gm::RA, Gm::CB>;
+    constexpr int nA = 4 + lg2(Pc::RAP), nB = 4 + lg2(Gm::CB), n = nA + nB;
+    static_assert(n >= 10 && n <= 12, "piece of 1 to 4 KiB");
     Mfma8Extra ex{};
+    ex.hiA = a.maskA & ~pdep_host(Gm::WM - 1, a.maskA);
+    ex.hiB = a.maskB & ~pdep_host(Gm::WN - 1, a.maskB);
     for (int rb = 0; rb < 8; ++rb) ex.dA[rb] = pdep_host(uint64_t(16 * rb), a.maskA);
     for (int v = 0; v < 4; ++v) ex.dV[v] = pdep_host(uint64_t(v), a.maskA);
     for (int cb = 0; cb < 4; ++cb) ex.dB[cb] = pdep_host(uint64_t(16 * cb), a.maskB);
@@ -598,45 +659,83 @@ Mfma8Extra extra_of(const StepArgs& a) {
         ex.sel[1] = 0x07060302u;  // neighbour v2, neighbour v3, own v2, own v3
     } else {
         ex.mode = 2;
+        return ex;
     }
-    // lane bit holding C bit pos (modes 0 and 1), -1 if none
-    auto lane_bit_of = [&](int pos) -> int {
-        const bool fromA = (a.maskA >> pos) & 1;
-        const int idx = __builtin_popcountll((fromA ? a.maskA : a.maskB) & ((uint64_t(1) << pos) - 1));
-        if (fromA) {
-            if (idx == 2 || idx == 3) return 4 + (idx - 2);
-            return idx == 1 && ex.mode == 1 ? 0 : -1;
+    // the piece's bits in C's order: C bit of A index bit i / B index bit j,
+    // and its rank among them
+    uint64_t posA[nA], posB[nB], all = 0;
+    for (int i = 0; i < nA; ++i) all |= posA[i] = pdep_host(uint64_t(1) << i, a.maskA);
+    for (int j = 0; j < nB; ++j) all |= posB[j] = pdep_host(uint64_t(1) << j, a.maskB);
+    const auto rank_of = [&](uint64_t pos) { return __builtin_popcountll(all & (pos - 1)); };
+    // lane bits: B index bits 0..3 and A index bits 2, 3; in mode 1 lane bit
+    // 0 stands for A index bit 1
+    int lr[6];
+    for (int k = 0; k < 4; ++k) lr[k] = rank_of(posB[k]);
+    lr[4] = rank_of(posA[2]);
+    lr[5] = rank_of(posA[3]);
+    if (ex.mode == 1) lr[0] = rank_of(posA[1]);
+    // M: chunk index bit c >= 4 (index bit c + 4) is XORed into the low four
+    // bits as M[c - 4]; a lane bit up there takes a low bit that no other lane
+    // bit has
+    uint32_t M[4] = {0, 0, 0, 0}, used = 0;
+    for (int k = 0; k < 6; ++k)
+        if (lr[k] >= 4 && lr[k] < 8) used |= 1u << (lr[k] - 4);
+    for (int k = 0; k < 6; ++k)
+        if (lr[k] >= 8) {
+            const uint32_t low = ~used & 15u, bit = low & (~low + 1);
+            M[lr[k] - 8] = bit;
+            used |= bit;
         }
-        if (idx >= 1 && idx <= 3) return idx;
-        return idx == 0 && ex.mode == 0 ? 0 : -1;
+    // byte place of an index bit
+    const auto place = [&](int rank) -> uint32_t {
+        uint32_t x = 1u << rank;
+        if (rank >= 8) x ^= M[rank - 8] << 4;
+        return x;
     };
-    ex.x2 = ex.x3 = -1;
-    if (ex.mode != 2) {
-        const int b2 = lane_bit_of(2), b3 = lane_bit_of(3);
-        if (b2 >= 0 && b3 >= 0 && b2 != b3) {
-            ex.x2 = b2;
-            ex.x3 = b3;
-        }
-    }
-    // the compiled 16-byte variants: (pair exchange, lane bit of C bit 2, of
-    // C bit 3) with bits 4 and 5 by permlane swaps and 0..3 at run time
-    const int c2 = ex.x2 >= 4 ? ex.x2 : 0, c3 = ex.x3 >= 4 ? ex.x3 : 0;
-    ex.form = 0;
-    if (ex.x2 >= 0) {
-        if (ex.mode == 0 && c2 == 4 && c3 == 5) ex.form = 1;
-        else if (ex.mode == 0 && c2 == 4 && c3 == 0) ex.form = 2;
-        else if (ex.mode == 0 && c2 == 0 && c3 == 4) ex.form = 3;
-        else if (ex.mode == 0 && c2 == 0 && c3 == 0) ex.form = 4;
-        else if (ex.mode == 1 && c2 == 0 && c3 == 4) ex.form = 5;
-        else if (ex.mode == 1 && c2 == 0 && c3 == 0) ex.form = 6;
-    }
-    if (ex.form == 0) ex.x2 = ex.x3 = -1;  // the lane offsets of 4-byte stores
+    for (int k = 0; k < 6; ++k) ex.sLane[k] = place(lr[k]);
+    for (int rb = 0; rb < Pc::RAP; ++rb)
+        for (int i = 4; i < nA; ++i)
+            if ((rb >> (i - 4)) & 1) ex.sRb[rb] ^= place(rank_of(posA[i]));
+    for (int cb = 0; cb < Gm::CB; ++cb)
+        for (int j = 4; j < nB; ++j)
+            if ((cb >> (j - 4)) & 1) ex.sCb[cb] ^= place(rank_of(posB[j]));
+    ex.rM[0] = M[0] << 4;
+    ex.rM[1] = M[1] << 4;
+    const auto pos_of = [&](int rank) { return pdep_host(uint64_t(1) << rank, all); };
+    for (int k = 0; k < 6; ++k) ex.cLane[k] = pos_of(4 + k);
+    for (int t = 0; t < Pc::NT; ++t)
+        for (int k = 0; k < 2; ++k)
+            if ((t >> k) & 1) {
+                ex.rT[t] ^= place(10 + k);
+                ex.cT[t] |= pos_of(10 + k);
+            }
+    ex.cPiece = pdep_host(uint64_t(16 * Pc::RAP), a.maskA);
     return ex;
+}
+
+// A grid that fills the GPU once: the work-groups walk the tiles of every
+// plane, so that only their first tile waits for its first stages unhidden
+// (launched per plane with 1024 work-groups, a group had 4 to 32 tiles).
+constexpr uint32_t kCUs = 256;
+template <class Gm, int NST, int RED>
+void launch_nst(const StepArgs& a, const Mfma8Extra& ex, int G, uint64_t T, int splits, int8_t* part,
+               int64_t scratch_per_plane, hipStream_t stream) {
+    static const int per_cu = [] {
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)k_mfma8<Gm, NST, RED>, Gm::THREADS, 0) !=
+            hipSuccess)
+            n = 1;
+        return std::max(n, 1);
+    }();
+    const dim3 grid(uint32_t(std::min<uint64_t>(T * uint64_t(G), uint64_t(kCUs) * uint64_t(per_cu))), uint32_t(splits),
+                    1);
+    hipLaunchKernelGGL((k_mfma8<Gm, NST, RED>), grid, dim3(Gm::THREADS), 0, stream, a, ex, G, splits, part,
+                       scratch_per_plane);
 }
 
 template <class Gm>
 hipError_t launch_cfg(const StepArgs& a, int G, hipStream_t stream, char* scratch, int64_t scratch_per_plane) {
-    const Mfma8Extra ex = extra_of(a);
+    const Mfma8Extra ex = extra_of<Gm>(a);
     const uint64_t T = (uint64_t(1) << (a.fA - Gm::LGM)) * (uint64_t(1) << (a.fB - Gm::LGN));
     // too few output tiles to fill the GPU: split K over block rows (powers
     // of two, as many partial tiles per plane as the scratch area holds, at
@@ -647,21 +746,19 @@ hipError_t launch_cfg(const StepArgs& a, int G, hipStream_t stream, char* scratc
     int splits = 1;
     while (T * G * splits * 2 <= 1024 && splits * 16 <= nk && T * splits * 2 <= cap_tiles) splits *= 2;
     int8_t* part = reinterpret_cast<int8_t*>(scratch);
-    dim3 grid(uint32_t(std::min<uint64_t>(T, 1024)), uint32_t(splits), G);
-    const int per = nk / splits;
-    // sums of at most 8 stages stay below 8 64 127^2 < 2^23: no fold
+    const int per = nk / splits;  // steps of 64 entries
+    // (the bias takes four registers that the largest tile does not have)
+    constexpr int RED = Gm::RA * Gm::CB == 32 ? RED_PLAIN : RED_BIAS;
     if (per > 8)
-        hipLaunchKernelGGL((k_mfma8<Gm, 4, true>), grid, dim3(Gm::THREADS), 0, stream, a, ex, splits, part,
-                           scratch_per_plane);
-    else if (per >= 4)
-        hipLaunchKernelGGL((k_mfma8<Gm, 4, false>), grid, dim3(Gm::THREADS), 0, stream, a, ex, splits, part,
-                           scratch_per_plane);
+        launch_nst<Gm, 4, RED_FOLD>(a, ex, G, T, splits, part, scratch_per_plane, stream);
+    else if (per == 8)
+        launch_nst<Gm, 4, RED_PLAIN>(a, ex, G, T, splits, part, scratch_per_plane, stream);
+    else if (per == 4)
+        launch_nst<Gm, 2, RED>(a, ex, G, T, splits, part, scratch_per_plane, stream);
     else if (per == 2)
-        hipLaunchKernelGGL((k_mfma8<Gm, 2, false>), grid, dim3(Gm::THREADS), 0, stream, a, ex, splits, part,
-                           scratch_per_plane);
+        launch_nst<Gm, 1, RED>(a, ex, G, T, splits, part, scratch_per_plane, stream);
     else
-        hipLaunchKernelGGL((k_mfma8<Gm, 1, false>), grid, dim3(Gm::THREADS), 0, stream, a, ex, splits, part,
-                           scratch_per_plane);
+        launch_nst<Gm, 0, RED>(a, ex, G, T, splits, part, scratch_per_plane, stream);
     if (splits > 1) {
         const uint64_t n = T * uint64_t(Gm::WM * Gm::WN);
         dim3 gr(uint32_t(std::min<uint64_t>((n + 255) / 256, 4096)), 1, G);
@@ -674,7 +771,7 @@ template <class Gm, int S>
 hipError_t launch_short(const StepArgs& a, int G, hipStream_t stream) {
     const uint64_t T = (uint64_t(1) << (a.fA - Gm::LGM)) * (uint64_t(1) << (a.fB - Gm::LGN));
     dim3 grid(uint32_t(std::min<uint64_t>(T, 2048)), 1, G);
-    hipLaunchKernelGGL((k_mfma8_short<Gm, S>), grid, dim3(Gm::THREADS), 0, stream, a, extra_of(a));
+    hipLaunchKernelGGL((k_mfma8_short<Gm, S>), grid, dim3(Gm::THREADS), 0, stream, a, extra_of<Gm>(a));
     return hipGetLastError();
 }
 
@@ -706,9 +803,21 @@ int mfma8_rule_cfg(const StepArgs& a) {
     return a.fA >= 8 ? MFMA8_256x64 : MFMA8_128x64;
 }
 
-hipError_t launch_mfma8_cfg(const StepArgs& a, int G, hipStream_t stream, char* scratch, int64_t scratch_per_plane,
+hipError_t launch_mfma8_cfg(const StepArgs& a0, int G, hipStream_t stream, char* scratch, int64_t scratch_per_plane,
                             int cfg) {
-    if (!mfma8_eligible(a) || (cfg != MFMA8_RULE && !mfma8_cfg_fits(cfg, a.fA, a.fB))) return hipErrorInvalidValue;
+    if (!mfma8_eligible(a0) || (cfg != MFMA8_RULE && !mfma8_cfg_fits(cfg, a0.fA, a0.fB))) return hipErrorInvalidValue;
+    StepArgs a = a0;
+    // C's two lowest bits are B's: with the operands exchanged they are A's
+    // and outputs leave as words instead of bytes (tiles of 128 x 128 or more
+    // take either side as A)
+    if ((a.maskB & 3) == 3 && a.fB >= 7) {
+        std::swap(a.A, a.B);
+        std::swap(a.strideA, a.strideB);
+        std::swap(a.maskA, a.maskB);
+        std::swap(a.fA, a.fB);
+        if (cfg == MFMA8_RULE && a.s >= 6) cfg = a.fA >= 8 && a.fB >= 8 ? MFMA8_256x256 : MFMA8_128x128;
+        if (cfg == MFMA8_256x128 || cfg == MFMA8_256x64) cfg = MFMA8_128x128;
+    }
     if (a.s < 6)
         return a.fB >= 7 ? launch_short_s<Cfg128x128>(a, G, stream) : launch_short_s<Cfg128x64>(a, G, stream);
     if (cfg == MFMA8_RULE) cfg = mfma8_rule_cfg(a);
