@@ -126,8 +126,14 @@ extern "C" tn_status tn_autotune(const char* out_path, void* workspace, size_t w
                                 &ok);
                     if (!ok) return TN_EHIP;
                     us[size_t(cfg)] = t / G;
-                    if (best < 0 || t < us[size_t(best)] * G) best = cfg;
                 }
+                // the rule's shape unless another one is clearly faster: a
+                // shape stands for its untuned neighbours too
+                best = mfma8_rule_cfg(a);
+                for (int cfg = 0; cfg < MFMA8_CFGS; ++cfg)
+                    if (us[size_t(cfg)] >= 0 && us[size_t(cfg)] < us[size_t(best)] &&
+                        us[size_t(cfg)] < 0.95 * us[size_t(mfma8_rule_cfg(a))])
+                        best = cfg;
                 tune_set(TK_MFMA8, EL_I8, fA, fB, s, best);
                 std::string u;
                 for (int cfg = 0; cfg < MFMA8_CFGS; ++cfg)

@@ -35,11 +35,19 @@ int64_t work_of(const Step& st) {
 
 int64_t lds_size(int rank) { return std::max<int64_t>(16, int64_t(1) << rank); }
 
-// Tensors of at least this many entries are laid out at multiples of it: the
-// matrix-core kernels read and write them in rows and tiles of powers of two.
-// At offsets of any multiple of 64 entries the largest 1-in-3 plan (n = 300,
-// 11 planes) took 103.7 ms, at these 98.5 ms.
-constexpr int64_t kBig = int64_t(1) << 20;
+// Tensors of a class lie at multiples of its unit, in a part of the arena of
+// their own: the matrix-core kernels read rows in lines of 128 bytes, and write
+// tiles of powers of two. At offsets of any multiple of 64 entries the largest
+// 1-in-3 plan (n = 300, 11 planes) took 103.7 ms, with tensors of 2^20 entries
+// and more at multiples of that 98.5 ms. Sizes are powers of two, so the first
+// fit keeps the multiples.
+constexpr int kClasses = 3;
+constexpr int64_t kUnit[kClasses] = {256, int64_t(1) << 12, int64_t(1) << 20};
+int class_of(int rank) {
+    int c = 0;
+    while (c + 1 < kClasses && (int64_t(1) << rank) >= kUnit[c + 1]) ++c;
+    return c;
+}
 
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
@@ -191,26 +199,23 @@ void build_exec(const Plan& plan, int es, Exec& ex) {
         ex.n_entries += uint32_t(align_up(pg.n_init, 16));
     }
     // arena: the programs' results live from the start, then the other
-    // steps in plan order. Large tensors have a part of their own behind the
-    // small ones, where every offset is a multiple of kBig: sizes are powers
-    // of two, so the first-fit keeps them aligned.
-    Arena small, big;
+    // steps in plan order; a part per size class
+    Arena part[kClasses];
     std::vector<int64_t> goff(size_t(n_ids), -1);
-    const auto is_big = [](int rank) { return (int64_t(1) << rank) >= kBig; };
     const auto take = [&](int rank) {
-        return is_big(rank) ? big.alloc(int64_t(1) << rank) : small.alloc(align_up(int64_t(1) << rank, kAlignElems));
+        const int c = class_of(rank);
+        return part[c].alloc(align_up(int64_t(1) << rank, kUnit[c]));
     };
     const auto drop = [&](int64_t off, int rank) {
-        if (is_big(rank))
-            big.release(off, int64_t(1) << rank);
-        else
-            small.release(off, align_up(int64_t(1) << rank, kAlignElems));
+        const int c = class_of(rank);
+        part[c].release(off, align_up(int64_t(1) << rank, kUnit[c]));
     };
     for (size_t i = 0; i < ex.progs.size(); ++i) {
         const Step& st = plan.steps[size_t(root_step[i])];
         if (ex.progs[i].final) continue;
         goff[size_t(st.out)] = take(st.rC);
         ex.progs[i].root_off = goff[size_t(st.out)];
+        ex.progs[i].root_rank = st.rC;
     }
     std::vector<int64_t> ioff(size_t(n_init), -1);
     for (int32_t k = 0; k < n_steps; ++k) {
@@ -236,13 +241,24 @@ void build_exec(const Plan& plan, int es, Exec& ex) {
         }
         ex.steps.push_back(st);
     }
-    const int64_t big0 = big.high > 0 ? align_up(small.high, kBig) : small.high;
-    for (Step& st : ex.steps) {
-        if (!st.initA && is_big(st.rA)) st.offA += big0;
-        if (!st.initB && is_big(st.rB)) st.offB += big0;
-        if (is_big(st.rC)) st.offC += big0;
+    // parts one after the other
+    int64_t base[kClasses], end = 0;
+    for (int c = 0; c < kClasses; ++c) {
+        base[c] = part[c].high > 0 ? align_up(end, kUnit[c]) : end;
+        end = base[c] + part[c].high;
     }
-    ex.arena_elems = std::max<int64_t>(big0 + big.high, kAlignElems);
+    for (FuseProg& pg : ex.progs)
+        if (!pg.final) pg.root_off += base[class_of(pg.root_rank)];
+    for (Step& st : ex.steps) {
+        if (!st.initA) st.offA += base[class_of(st.rA)];
+        if (!st.initB) st.offB += base[class_of(st.rB)];
+        st.offC += base[class_of(st.rC)];
+    }
+    // planes keep the largest class's multiples
+    int64_t unit = kUnit[0];
+    for (int c = 0; c < kClasses; ++c)
+        if (part[c].high > 0) unit = kUnit[c];
+    ex.arena_elems = std::max<int64_t>(align_up(end, unit), kAlignElems);
 }
 
 int64_t blob_bytes(const Exec& ex, bool wide) {

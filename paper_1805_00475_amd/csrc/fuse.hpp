@@ -32,7 +32,8 @@ struct FuseProg {
     uint32_t n_steps, n_items, n_levels;
     uint32_t final;                        // 1: the root is the whole network's scalar
     int64_t root_off;                      // global output offset (entries), unless final
-    uint32_t lds_elems, pad;               // its LDS entries (the program follows them)
+    uint32_t lds_elems;                    // its LDS entries (the program follows them)
+    int32_t root_rank;
 };
 static_assert(sizeof(FuseStep) == 16 && sizeof(FuseProg) == 48, "device layout");
 

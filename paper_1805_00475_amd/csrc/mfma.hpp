@@ -44,6 +44,8 @@ hipError_t launch_mfma(const StepArgs& a, int G, hipStream_t stream, Profiler* p
 hipError_t launch_mfma8(const StepArgs& a, int G, hipStream_t stream, Profiler* prof, double step_bytes,
                         double step_macs, char* scratch, int64_t scratch_per_plane);
 bool mfma8_eligible(const StepArgs& a);
+// The tile shape of the built-in rule: the largest that fits both free sides.
+int mfma8_rule_cfg(const StepArgs& a);
 // The tiled int8 kernel with a given tile shape (Mfma8Cfg of tune.hpp;
 // MFMA8_RULE = the built-in rule), without profiling (the autotuner's
 // measurement launches).

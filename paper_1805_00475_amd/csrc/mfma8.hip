@@ -519,7 +519,11 @@ __global__ __launch_bounds__(G::THREADS, 1) void k_mfma8(StepArgs a, Mfma8Extra 
     }
 }
 
-// split-K: sum the partial residues of every K range and scatter into C
+// split-K: sum the partial residues of every K range and scatter into C; a
+// thread takes 16 consecutive A indices, whose C offsets differ by the same
+// 16 deposits everywhere (one output and two bit deposits per thread made
+// this kernel 5 times as long as the products: 144 us for 16 planes of rank
+// 20 against 24).
 template <class G>
 __global__ __launch_bounds__(256) void k_mfma8_reduce(StepArgs a, const int8_t* part, int64_t part_stride,
                                                       int splits) {
@@ -528,17 +532,25 @@ __global__ __launch_bounds__(256) void k_mfma8_reduce(StepArgs a, const int8_t* 
     int8_t* C = static_cast<int8_t*>(a.C) + g * a.strideC;
     const int lgA = a.fA - G::LGM, lgB = a.fB - G::LGN;
     const uint64_t T = uint64_t(1) << (lgA + lgB);
-    const uint64_t n = T * (G::WM * G::WN);
+    const uint64_t n = T * (G::WM * G::WN / 16);
     const int8_t* pg = part + g * part_stride;
+    uint64_t off[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) off[v] = pdep64(uint64_t(v), a.maskA);
     for (uint64_t e = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < n; e += uint64_t(gridDim.x) * blockDim.x) {
-        const uint64_t tile = e / (G::WM * G::WN), loc = e % (G::WM * G::WN);  // loc = j WM + i
-        int32_t sum = 0;  // at most 1024 residues of magnitude 127
-        for (int y = 0; y < splits; ++y) sum += pg[(uint64_t(y) * T + tile) * (G::WM * G::WN) + loc];
+        const uint64_t tile = e / (G::WM * G::WN / 16), loc = 16 * (e % (G::WM * G::WN / 16));  // loc = j WM + i
+        int32_t sum[16] = {};  // at most 1024 residues of magnitude 127
+        for (int y = 0; y < splits; ++y) {
+            const v4i x = *reinterpret_cast<const v4i*>(pg + (uint64_t(y) * T + tile) * (G::WM * G::WN) + loc);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[v] += int32_t(int8_t(x[v / 4] >> (8 * (v % 4))));
+        }
         uint32_t ta, tb;
         tile_coords_lg(uint32_t(tile), lgA, lgB, ta, tb);
         const uint64_t j = loc / G::WM, i = loc % G::WM;
-        C[pdep64(uint64_t(ta) * G::WM + i, a.maskA) | pdep64(uint64_t(tb) * G::WN + j, a.maskB)] =
-            int8_t(ms.center32(sum));
+        int8_t* const out = C + (pdep64(uint64_t(ta) * G::WM + i, a.maskA) | pdep64(uint64_t(tb) * G::WN + j, a.maskB));
+#pragma unroll
+        for (int v = 0; v < 16; ++v) out[off[v]] = int8_t(ms.center32(sum[v]));
     }
 }
 
@@ -737,14 +749,15 @@ template <class Gm>
 hipError_t launch_cfg(const StepArgs& a, int G, hipStream_t stream, char* scratch, int64_t scratch_per_plane) {
     const Mfma8Extra ex = extra_of<Gm>(a);
     const uint64_t T = (uint64_t(1) << (a.fA - Gm::LGM)) * (uint64_t(1) << (a.fB - Gm::LGN));
-    // too few output tiles to fill the GPU: split K over block rows (powers
-    // of two, as many partial tiles per plane as the scratch area holds, at
-    // least 8 stages each so that reading operands outweighs writing the
-    // partial tile)
+    // too few output tiles to fill the GPU (one work-group of the larger tiles
+    // per CU, two of the others): split K over block rows (powers of two, as
+    // many partial tiles per plane as the scratch area holds, at least 8 steps
+    // each so that reading operands outweighs writing the partial tile)
     const int nk = 1 << (a.s - 6);
+    const uint64_t fill = kCUs * (Gm::WM * Gm::WN > 128 * 128 ? 1 : 2);
     const uint64_t cap_tiles = uint64_t(scratch_per_plane) / uint64_t(Gm::WM * Gm::WN);
     int splits = 1;
-    while (T * G * splits * 2 <= 1024 && splits * 16 <= nk && T * splits * 2 <= cap_tiles) splits *= 2;
+    while (T * G * splits * 2 <= fill && splits * 16 <= nk && T * splits * 2 <= cap_tiles) splits *= 2;
     int8_t* part = reinterpret_cast<int8_t*>(scratch);
     const int per = nk / splits;  // steps of 64 entries
     // (the bias takes four registers that the largest tile does not have)
@@ -760,7 +773,7 @@ hipError_t launch_cfg(const StepArgs& a, int G, hipStream_t stream, char* scratc
     else
         launch_nst<Gm, 0, RED>(a, ex, G, T, splits, part, scratch_per_plane, stream);
     if (splits > 1) {
-        const uint64_t n = T * uint64_t(Gm::WM * Gm::WN);
+        const uint64_t n = T * uint64_t(Gm::WM * Gm::WN / 16);
         dim3 gr(uint32_t(std::min<uint64_t>((n + 255) / 256, 4096)), 1, G);
         hipLaunchKernelGGL((k_mfma8_reduce<Gm>), gr, dim3(256), 0, stream, a, part, scratch_per_plane, splits);
     }
@@ -796,7 +809,6 @@ bool mfma8_eligible(const StepArgs& a) {
     return a.s >= 0 && a.s <= k8MaxRowBytesLog && a.fA >= 7 && a.fB >= 6 && a.fA + a.fB <= 45;
 }
 
-// The tile shape of the built-in rule: the largest that fits both free sides.
 int mfma8_rule_cfg(const StepArgs& a) {
     if (a.fB >= 8) return MFMA8_256x256;
     if (a.fB == 7) return a.fA >= 8 ? MFMA8_256x128 : MFMA8_128x128;
