@@ -20,11 +20,14 @@ struct Limits {
 
 // A work-group does about 30 multiply-adds per clock on bytes and 4 on 64-bit
 // words, so these programs end within a few launch times; LDS is held to 96
-// KB, one group per CU (a plan has 1 to 30 programs per plane).
+// KB (most programs take less than 12). Measured with half and twice the work:
+// vertex cover n = 60 82 / 53 / 53 us (2^15, 2^17, 2^18), hard-core n = 100 534 /
+// 489 / 498 us (2^16 and rank 12, 2^17, 2^18), vertex cover n = 120 95 / 93 / 93
+// us (2^16, 2^17, 2^18).
 Limits limits_of(int es) {
     if (es == 1) return {13, int64_t(1) << 17, int64_t(96) << 10};
-    if (es == 4) return {12, int64_t(1) << 16, int64_t(24) << 10};
-    return {11, int64_t(1) << 16, int64_t(12) << 10};
+    if (es == 4) return {13, int64_t(1) << 17, int64_t(24) << 10};
+    return {12, int64_t(1) << 17, int64_t(12) << 10};
 }
 
 // Work of a step for one work-group, in multiply-adds: every output costs
