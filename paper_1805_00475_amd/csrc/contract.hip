@@ -366,9 +366,11 @@ KernelClass choose_class(const Step& st, int el, int flags) {
     a.fA = std::max(st.rA, st.rB) - st.s;  // the larger free side plays A
     a.fB = std::min(st.rA, st.rB) - st.s;
     if (flags & TN_FLAG_GENERIC_ONLY) return KC_GENERIC;
-    if (a.rC <= 6 && a.s >= 10) return KC_DOT;
+    const bool narrow32 = el == EL_U32 && !(flags & TN_FLAG_NO_MFMA) && narrow32_eligible(a);
+    if (a.rC <= 6 && a.s >= 10 && !narrow32) return KC_DOT;
     if (el != EL_U64 && !st.initA && !st.initB && mfma_eligible(a, el) && !(flags & TN_FLAG_NO_MFMA)) return KC_MFMA;
     if (el == EL_I8 && narrow8_eligible(a) && !(flags & TN_FLAG_NO_MFMA)) return KC_NARROW;
+    if (narrow32) return KC_NARROW;
     if (a.s <= 5 && a.fA >= 8) return KC_STREAM;
     if (a.s >= 6) return KC_ROWDOT;
     return KC_GENERIC;
@@ -475,6 +477,8 @@ hipError_t launch_step(const Step& st0, int el, int flags, const uint32_t* prime
     }
     if (pick == KC_NARROW) {
         *kc = KC_NARROW;
+        if (el == EL_U32)
+            return launch_narrow32(a, G, stream, &prof, step_bytes, step_macs, scratch, kScratchPerPrime);
         return launch_narrow8(a, G, stream, &prof, step_bytes, step_macs, scratch, kScratchPerPrime);
     }
     if (pick == KC_MFMA) {

@@ -57,5 +57,9 @@ hipError_t launch_mfma8_cfg(const StepArgs& a, int G, hipStream_t stream, char* 
 hipError_t launch_narrow8(const StepArgs& a, int G, hipStream_t stream, Profiler* prof, double step_bytes,
                           double step_macs, char* scratch, int64_t scratch_per_plane);
 bool narrow8_eligible(const StepArgs& a);
+// The same for residues modulo 16-bit primes (narrow32.hip).
+hipError_t launch_narrow32(const StepArgs& a, int G, hipStream_t stream, Profiler* prof, double step_bytes,
+                           double step_macs, char* scratch, int64_t scratch_per_plane);
+bool narrow32_eligible(const StepArgs& a);
 
 }  // namespace tn
