@@ -15,6 +15,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "internal.hpp"
@@ -45,6 +46,15 @@ __device__ __forceinline__ void load_planes(const StepArgs& a, const void*& A, c
 __device__ __forceinline__ ModSmall mod_small(const StepArgs& a) {
     const int g = blockIdx.z;
     return ModSmall{int32_t(a.p[g]), a.r2[g], a.r16[g], a.pinv[g]};
+}
+
+// 16 int8 products: four 4-way dot products, at most 16 127^2 < 2^18.
+typedef int v4i_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int dot16(v4i_t x, v4i_t y) {
+    int d = __builtin_amdgcn_sdot4(x[0], y[0], 0, false);
+    d = __builtin_amdgcn_sdot4(x[1], y[1], d, false);
+    d = __builtin_amdgcn_sdot4(x[2], y[2], d, false);
+    return __builtin_amdgcn_sdot4(x[3], y[3], d, false);
 }
 
 // Any shape: one thread per output entry, bit gathers by loops.
@@ -91,12 +101,30 @@ __global__ __launch_bounds__(256) void k_generic(StepArgs a) {
 // Streaming step, small shared dimension (K = 2^LOGK <= 32): each thread
 // owns one xA (256 consecutive xA per block iteration, so A is read once,
 // coalesced) and NB consecutive xB of the block's xB chunk; the B slab is
-// uniform across the block. Output positions split into a uniform part
-// (block's xA base and xB chunk) and per-lane / per-j parts deposited once.
+// uniform across the block and read by scalar loads (through the constant
+// address space: nothing writes it during the step, but the compiler can not
+// know that C is not B). Output positions split into a uniform part
+// (block's xA base and xB chunk) and per-lane / per-j parts.
+//
+// Bit deposits by loops over the mask took most of the time of a step (131072
+// work-groups of one iteration each; rank 26 x 2 over K = 2 on bytes: 483 us for
+// 96 MB). So work-groups walk several iterations, deposits are formed by
+// addition, dep(x + y) = ((dep(x) | ~mask) + dep(y)) & mask, and the masks of
+// lanes and strides come from the host: that step 66 us, rank 24 x 9 over K = 2^5 modulo
+// a 16-bit prime 58 -> 44 us, rank 27 x 6 over K = 2^5 on bytes 62 -> 27 us.
+struct StreamExtra {
+    uint64_t lane[8];  // C offsets of the lane's bits
+    uint64_t hi, step; // maskA without those bits; C offset of gridDim.x << 8
+};
+
 template <int E, int LOGK, int NB>
-__global__ __launch_bounds__(256) void k_stream(StepArgs a) {
+__global__ __launch_bounds__(256) void k_stream(StepArgs a, StreamExtra ex) {
     using T = typename ElemT<E>::T;
     constexpr int K = 1 << LOGK;
+    // int8 entries travel and multiply as words of four
+    constexpr bool kWords = E == EL_I8 && K >= 4;
+    using W = std::conditional_t<kWords, int, T>;
+    constexpr int KW = kWords ? K / 4 : K;
     const void *pA, *pB;
     void* pC;
     load_planes<E>(a, pA, pB, pC);
@@ -106,23 +134,30 @@ __global__ __launch_bounds__(256) void k_stream(StepArgs a) {
     const ModP m{a.p[blockIdx.z], a.r2[blockIdx.z]};
     const ModSmall ms = mod_small(a);
     const uint64_t lane = threadIdx.x;
-    const uint64_t laneC = pdep64(lane, a.maskA);
-    uint64_t offB[NB];
+    uint64_t laneC = 0;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) offB[j] = pdep64(uint64_t(j), a.maskB);
+    for (int k = 0; k < 8; ++k) laneC |= (lane >> k) & 1 ? ex.lane[k] : 0;
+    uint64_t offB[NB];
+    offB[0] = 0;
+#pragma unroll
+    for (int j = 1; j < NB; ++j) offB[j] = (offB[j - 1] - a.maskB) & a.maskB;
     const uint64_t n_iter = (uint64_t(1) << a.fA) >> 8;
     const uint64_t n_chunk = (uint64_t(1) << a.fB) / NB;
+    const uint64_t first = pdep_from(blockIdx.x, ex.hi);
     for (uint64_t cb = blockIdx.y; cb < n_chunk; cb += gridDim.y) {
         const uint64_t xb0 = cb * NB;
-        const uint64_t baseB = pdep64(xb0, a.maskB);
-        const T* rb = B + (xb0 << LOGK);
-        for (uint64_t it = blockIdx.x; it < n_iter; it += gridDim.x) {
+        const uint64_t baseB = laneC | pdep_from(uint32_t(xb0), a.maskB);
+        typedef const __attribute__((address_space(4))) W* cptr_t;
+        const cptr_t rb = (cptr_t)(uintptr_t)(B + (xb0 << LOGK));
+        uint64_t itC = first;
+        for (uint64_t it = blockIdx.x; it < n_iter; it += gridDim.x, itC = ((itC | ~ex.hi) + ex.step) & ex.hi) {
             const uint64_t xA = (it << 8) | lane;
-            const uint64_t cA = pdep64(it << 8, a.maskA) | laneC | baseB;
-            T av[K];
-            const T* ra = A + (xA << LOGK);
+            const uint64_t cA = itC | baseB;
+            W av[KW];
+            const W* ra = reinterpret_cast<const W*>(
+                __builtin_assume_aligned(A + (xA << LOGK), K * sizeof(T) < 16 ? K * sizeof(T) : 16));
 #pragma unroll
-            for (int z = 0; z < K; ++z) av[z] = ra[z];
+            for (int z = 0; z < KW; ++z) av[z] = ra[z];
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
                 if constexpr (E == EL_U64) {
@@ -134,16 +169,20 @@ __global__ __launch_bounds__(256) void k_stream(StepArgs a) {
                     // at most 32 products of magnitude 2^14: int32 is exact
                     int32_t acc = 0;
 #pragma unroll
-                    for (int z = 0; z < K; ++z) acc += int32_t(av[z]) * int32_t(rb[j * K + z]);
+                    for (int z = 0; z < KW; ++z) {
+                        if constexpr (kWords)
+                            acc = __builtin_amdgcn_sdot4(av[z], rb[j * KW + z], acc, false);
+                        else
+                            acc += int32_t(av[z]) * int32_t(rb[j * K + z]);
+                    }
                     C[cA | offB[j]] = T(ms.center32(acc));
                 } else {
+                    // at most 32 products below 2^32: one fold brings the sum
+                    // below 2^33
                     uint64_t acc = 0;
 #pragma unroll
-                    for (int z = 0; z < K; ++z) {
-                        acc += uint64_t(av[z]) * rb[j * K + z];
-                        if (z % 3 == 2) acc = m.fold(acc);
-                    }
-                    C[cA | offB[j]] = m.finish(acc);
+                    for (int z = 0; z < K; ++z) acc += uint64_t(av[z]) * rb[j * K + z];
+                    C[cA | offB[j]] = m.finish33(m.fold(acc));
                 }
             }
         }
@@ -179,19 +218,10 @@ __global__ __launch_bounds__(256) void k_rowdot(StepArgs a) {
             int64_t acc = 0;
             if (K >= 1024) {
                 // 16 bytes per lane and iteration (rows start 64-byte
-                // aligned), four 4-way int8 dot products; a chunk's sum is at
-                // most 16 127^2 < 2^18, widened once per chunk
-                typedef int v4i_t __attribute__((ext_vector_type(4)));
+                // aligned), widened once per chunk
                 const v4i_t* va = reinterpret_cast<const v4i_t*>(ra);
                 const v4i_t* vb = reinterpret_cast<const v4i_t*>(rb);
-                for (uint64_t z = lane; z < K / 16; z += 64) {
-                    const v4i_t x = va[z], y = vb[z];
-                    int d = __builtin_amdgcn_sdot4(x[0], y[0], 0, false);
-                    d = __builtin_amdgcn_sdot4(x[1], y[1], d, false);
-                    d = __builtin_amdgcn_sdot4(x[2], y[2], d, false);
-                    d = __builtin_amdgcn_sdot4(x[3], y[3], d, false);
-                    acc += d;
-                }
+                for (uint64_t z = lane; z < K / 16; z += 64) acc += dot16(va[z], vb[z]);
             } else {
                 for (uint64_t z = lane; z < K; z += 64) acc += int32_t(ra[z]) * int32_t(rb[z]);
             }
@@ -249,8 +279,13 @@ __global__ __launch_bounds__(256) void k_dot_partial(StepArgs a, uint64_t* scrat
             for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
             v = acc;
         } else if constexpr (E == EL_I8) {
+            // 16 bytes per lane, as in k_rowdot (slices are of at least 256;
+            // byte by byte 2^24 entries took 40 us, so 17)
+            const v4i_t* va = reinterpret_cast<const v4i_t*>(ra);
+            const v4i_t* vb = reinterpret_cast<const v4i_t*>(rb);
             int64_t acc = 0;
-            for (uint64_t z = threadIdx.x; z < slice; z += blockDim.x) acc += int32_t(ra[z]) * int32_t(rb[z]);
+#pragma unroll 4
+            for (uint64_t z = threadIdx.x; z < slice / 16; z += 256) acc += dot16(va[z], vb[z]);
             for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
             v = uint64_t(acc);
         } else {
@@ -311,26 +346,26 @@ __global__ __launch_bounds__(64) void k_dot_final(StepArgs a, const uint64_t* sc
 // ----------------------------------------------------------------- launches
 
 template <int E, int LOGK>
-hipError_t launch_stream_nb(int nb, dim3 grid, hipStream_t st, const StepArgs& a) {
+hipError_t launch_stream_nb(int nb, dim3 grid, hipStream_t st, const StepArgs& a, const StreamExtra& ex) {
     switch (nb) {
-        case 1: hipLaunchKernelGGL((k_stream<E, LOGK, 1>), grid, dim3(256), 0, st, a); break;
-        case 2: hipLaunchKernelGGL((k_stream<E, LOGK, 2>), grid, dim3(256), 0, st, a); break;
-        case 4: hipLaunchKernelGGL((k_stream<E, LOGK, 4>), grid, dim3(256), 0, st, a); break;
-        case 8: hipLaunchKernelGGL((k_stream<E, LOGK, 8>), grid, dim3(256), 0, st, a); break;
-        default: hipLaunchKernelGGL((k_stream<E, LOGK, 16>), grid, dim3(256), 0, st, a); break;
+        case 1: hipLaunchKernelGGL((k_stream<E, LOGK, 1>), grid, dim3(256), 0, st, a, ex); break;
+        case 2: hipLaunchKernelGGL((k_stream<E, LOGK, 2>), grid, dim3(256), 0, st, a, ex); break;
+        case 4: hipLaunchKernelGGL((k_stream<E, LOGK, 4>), grid, dim3(256), 0, st, a, ex); break;
+        case 8: hipLaunchKernelGGL((k_stream<E, LOGK, 8>), grid, dim3(256), 0, st, a, ex); break;
+        default: hipLaunchKernelGGL((k_stream<E, LOGK, 16>), grid, dim3(256), 0, st, a, ex); break;
     }
     return hipGetLastError();
 }
 
 template <int E>
-hipError_t launch_stream(int logk, int nb, dim3 grid, hipStream_t st, const StepArgs& a) {
-    switch (logk) {
-        case 0: return launch_stream_nb<E, 0>(nb, grid, st, a);
-        case 1: return launch_stream_nb<E, 1>(nb, grid, st, a);
-        case 2: return launch_stream_nb<E, 2>(nb, grid, st, a);
-        case 3: return launch_stream_nb<E, 3>(nb, grid, st, a);
-        case 4: return launch_stream_nb<E, 4>(nb, grid, st, a);
-        default: return launch_stream_nb<E, 5>(nb, grid, st, a);
+hipError_t launch_stream(int nb, dim3 grid, hipStream_t st, const StepArgs& a, const StreamExtra& ex) {
+    switch (a.s) {
+        case 0: return launch_stream_nb<E, 0>(nb, grid, st, a, ex);
+        case 1: return launch_stream_nb<E, 1>(nb, grid, st, a, ex);
+        case 2: return launch_stream_nb<E, 2>(nb, grid, st, a, ex);
+        case 3: return launch_stream_nb<E, 3>(nb, grid, st, a, ex);
+        case 4: return launch_stream_nb<E, 4>(nb, grid, st, a, ex);
+        default: return launch_stream_nb<E, 5>(nb, grid, st, a, ex);
     }
 }
 
@@ -345,18 +380,33 @@ hipError_t launch_stream(int logk, int nb, dim3 grid, hipStream_t st, const Step
             hipLaunchKernelGGL(kern<EL_U32>, grid, block, 0, stream, __VA_ARGS__);           \
     } while (0)
 
+// (2048, 4096 and 8192 measured within 10 % of each other, 4096 the fastest)
+constexpr uint64_t kStreamGroups = 4096;
 inline uint32_t cap32(uint64_t x, uint32_t hi) { return uint32_t(std::min<uint64_t>(std::max<uint64_t>(x, 1), hi)); }
 
 // The streaming kernel with 2^nb B rows per thread (nb <= min(fB, 4)),
-// without profiling (the autotuner's measurement launches).
+// without profiling (the autotuner's measurement launches). Work-groups in
+// a number that fills the GPU, a power of two in x so that a walk's stride is
+// one bit.
 hipError_t launch_stream_step(const StepArgs& a, int el, int G, int nb, hipStream_t st) {
     if (nb < 0 || nb > 4 || nb > a.fB || a.s > 5 || a.fA < 8) return hipErrorInvalidValue;
     const uint64_t n_iter = (uint64_t(1) << a.fA) >> 8;
-    const uint64_t n_chunk = (uint64_t(1) << a.fB) >> nb;
-    dim3 grid(cap32(n_iter, 1u << 20), cap32(n_chunk, 65535), uint32_t(G));
-    return el == EL_U64  ? launch_stream<EL_U64>(a.s, 1 << nb, grid, st, a)
-           : el == EL_I8 ? launch_stream<EL_I8>(a.s, 1 << nb, grid, st, a)
-                         : launch_stream<EL_U32>(a.s, 1 << nb, grid, st, a);
+    const uint32_t y = cap32((uint64_t(1) << a.fB) >> nb, 65535);
+    uint32_t x = 1;
+    while (x < n_iter && uint64_t(x) * y * uint64_t(G) < kStreamGroups) x *= 2;
+    StreamExtra ex{};
+    ex.hi = a.maskA;
+    for (int k = 0; k < 8; ++k) {
+        ex.lane[k] = ex.hi & (~ex.hi + 1);
+        ex.hi &= ex.hi - 1;
+    }
+    ex.step = ex.hi;
+    for (uint32_t k = x; k > 1; k /= 2) ex.step &= ex.step - 1;
+    ex.step &= ~ex.step + 1;  // no bit if one walk covers all
+    const dim3 grid(x, y, uint32_t(G));
+    return el == EL_U64  ? launch_stream<EL_U64>(1 << nb, grid, st, a, ex)
+           : el == EL_I8 ? launch_stream<EL_I8>(1 << nb, grid, st, a, ex)
+                         : launch_stream<EL_U32>(1 << nb, grid, st, a, ex);
 }
 
 KernelClass choose_class(const Step& st, int el, int flags) {
@@ -371,6 +421,7 @@ KernelClass choose_class(const Step& st, int el, int flags) {
     if (el != EL_U64 && !st.initA && !st.initB && mfma_eligible(a, el) && !(flags & TN_FLAG_NO_MFMA)) return KC_MFMA;
     if (el == EL_I8 && narrow8_eligible(a) && !(flags & TN_FLAG_NO_MFMA)) return KC_NARROW;
     if (narrow32) return KC_NARROW;
+    if (el == EL_I8 && !st.initA && !st.initB && short8_eligible(a) && !(flags & TN_FLAG_NO_MFMA)) return KC_NARROW;
     if (a.s <= 5 && a.fA >= 8) return KC_STREAM;
     if (a.s >= 6) return KC_ROWDOT;
     return KC_GENERIC;
@@ -479,6 +530,7 @@ hipError_t launch_step(const Step& st0, int el, int flags, const uint32_t* prime
         *kc = KC_NARROW;
         if (el == EL_U32)
             return launch_narrow32(a, G, stream, &prof, step_bytes, step_macs, scratch, kScratchPerPrime);
+        if (a.s < 6) return launch_short8(a, G, stream, &prof, step_bytes, step_macs);
         return launch_narrow8(a, G, stream, &prof, step_bytes, step_macs, scratch, kScratchPerPrime);
     }
     if (pick == KC_MFMA) {
@@ -490,14 +542,9 @@ hipError_t launch_step(const Step& st0, int el, int flags, const uint32_t* prime
         // B rows per thread: the autotuner's choice for the nearest tuned shape, else 2^min(fB, 4)
         const int tuned = tuned_choice(TK_STREAM, el, a.fA, a.fB, a.s);
         const int nb = tuned >= 0 ? std::min({tuned, a.fB, 4}) : std::min(a.fB, 4);
-        const uint64_t n_iter = (uint64_t(1) << a.fA) >> 8;
-        const uint64_t n_chunk = (uint64_t(1) << a.fB) >> nb;
-        dim3 grid(cap32(n_iter, 1u << 20), cap32(n_chunk, 65535), G);
         *kc = KC_STREAM;
         prof.before(stream);
-        hipError_t e = el == EL_U64  ? launch_stream<EL_U64>(a.s, 1 << nb, grid, stream, a)
-                       : el == EL_I8 ? launch_stream<EL_I8>(a.s, 1 << nb, grid, stream, a)
-                                     : launch_stream<EL_U32>(a.s, 1 << nb, grid, stream, a);
+        const hipError_t e = launch_stream_step(a, el, G, nb, stream);
         prof.after_raw(stream, KC_STREAM, step_bytes, step_macs);
         return e;
     }

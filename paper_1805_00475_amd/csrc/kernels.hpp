@@ -53,8 +53,8 @@ struct StepArgs {
 struct ModP {
     uint32_t p, r;
     __device__ __forceinline__ uint64_t fold(uint64_t x) const { return (x >> 32) * r + (x & 0xffffffffull); }
-    __device__ __forceinline__ uint32_t finish(uint64_t x) const {
-        x = fold(fold(x));
+    __device__ __forceinline__ uint32_t finish(uint64_t x) const { return finish33(fold(fold(x))); }
+    __device__ __forceinline__ uint32_t finish33(uint64_t x) const {  // x < 2^33
         const uint32_t r16 = 65536u - p;
         uint32_t y = uint32_t(x >> 16) * r16 + uint32_t(x & 0xffffu);  // < 2^28.01
         y = (y >> 16) * r16 + (y & 0xffffu);
@@ -94,11 +94,24 @@ struct ModSmall {
     }
 };
 
-// Scatter the low bits of x into the set bits of mask (bit deposit).
+// Scatter the low bits of x into the set bits of mask (bit deposit); ends with
+// the highest set bit of x.
 __device__ __forceinline__ uint64_t pdep64(uint64_t x, uint64_t mask) {
     uint64_t r = 0;
-    while (mask) {
+    while (x) {
         uint64_t low = mask & (~mask + 1);
+        if (x & 1) r |= low;
+        x >>= 1;
+        mask &= mask - 1;
+    }
+    return r;
+}
+
+// The same for a uniform 32-bit x (scalar compares end the loop).
+__device__ __forceinline__ uint64_t pdep_from(uint32_t x, uint64_t mask) {
+    uint64_t r = 0;
+    while (x) {
+        const uint64_t low = mask & (~mask + 1);
         if (x & 1) r |= low;
         x >>= 1;
         mask &= mask - 1;

@@ -57,7 +57,11 @@ hipError_t launch_mfma8_cfg(const StepArgs& a, int G, hipStream_t stream, char* 
 hipError_t launch_narrow8(const StepArgs& a, int G, hipStream_t stream, Profiler* prof, double step_bytes,
                           double step_macs, char* scratch, int64_t scratch_per_plane);
 bool narrow8_eligible(const StepArgs& a);
-// The same for residues modulo 16-bit primes (narrow32.hip).
+// K of at most 32 entries, a B side of 16 or 32 rows (mfma8.hip).
+hipError_t launch_short8(const StepArgs& a, int G, hipStream_t stream, Profiler* prof, double step_bytes,
+                         double step_macs);
+bool short8_eligible(const StepArgs& a);
+// The same as launch_narrow8 for residues modulo 16-bit primes (narrow32.hip).
 hipError_t launch_narrow32(const StepArgs& a, int G, hipStream_t stream, Profiler* prof, double step_bytes,
                            double step_macs, char* scratch, int64_t scratch_per_plane);
 bool narrow32_eligible(const StepArgs& a);

@@ -137,18 +137,6 @@ __device__ __forceinline__ uint32_t out_word(const v4i (&acc)[RA][CB], int rb, i
     return __builtin_amdgcn_perm(x, y, sel);
 }
 
-// Bit deposit of a (uniform) tile index: the loop ends with its highest set bit.
-__device__ __forceinline__ uint64_t pdep_from(uint32_t x, uint64_t mask) {
-    uint64_t r = 0;
-    while (x) {
-        const uint64_t low = mask & (~mask + 1);
-        if (x & 1) r |= low;
-        x >>= 1;
-        mask &= mask - 1;
-    }
-    return r;
-}
-
 // Bytes of LDS a wave's output piece takes, and pieces of its tile.
 template <int RA, int CB>
 struct Piece {
@@ -251,6 +239,12 @@ using Cfg256x128 = Cfg<256, 128, 8, 8, 2>;
 using Cfg128x128 = Cfg<128, 128, 8, 4, 2>;
 using Cfg256x64 = Cfg<256, 64, 4, 4, 4>;
 using Cfg128x64 = Cfg<128, 64, 4, 2, 4>;
+// short K only: few rows on one side
+using Cfg512x16 = Cfg<512, 16, 4, 8, 1>;
+using Cfg512x32 = Cfg<512, 32, 4, 8, 2>;
+using Cfg64x256 = Cfg<64, 256, 4, 4, 4>;
+using Cfg32x256 = Cfg<32, 256, 4, 2, 4>;
+using Cfg16x256 = Cfg<16, 256, 4, 1, 4>;
 
 // One step on int8 residues: the tiles of WM x WN outputs of all residue planes
 // are dealt round-robin to a grid that fills the GPU once, K split over
@@ -800,6 +794,14 @@ hipError_t launch_short_s(const StepArgs& a, int G, hipStream_t stream) {
     }
 }
 
+// A as B and B as A.
+void exchange(StepArgs& a) {
+    std::swap(a.A, a.B);
+    std::swap(a.strideA, a.strideB);
+    std::swap(a.maskA, a.maskB);
+    std::swap(a.fA, a.fB);
+}
+
 }  // namespace
 
 bool mfma8_eligible(const StepArgs& a) {
@@ -823,12 +825,14 @@ hipError_t launch_mfma8_cfg(const StepArgs& a0, int G, hipStream_t stream, char*
     // and outputs leave as words instead of bytes (tiles of 128 x 128 or more
     // take either side as A)
     if ((a.maskB & 3) == 3 && a.fB >= 7) {
-        std::swap(a.A, a.B);
-        std::swap(a.strideA, a.strideB);
-        std::swap(a.maskA, a.maskB);
-        std::swap(a.fA, a.fB);
+        exchange(a);
         if (cfg == MFMA8_RULE && a.s >= 6) cfg = a.fA >= 8 && a.fB >= 8 ? MFMA8_256x256 : MFMA8_128x128;
         if (cfg == MFMA8_256x128 || cfg == MFMA8_256x64) cfg = MFMA8_128x128;
+    }
+    // (a B side of 6 bits exchanges where K is short: tiles of 64 x 256)
+    if (a.s < 6 && a.fB == 6 && a.fA >= 8 && (a.maskB & 3) == 3) {
+        exchange(a);
+        return launch_short_s<Cfg64x256>(a, G, stream);
     }
     if (a.s < 6)
         return a.fB >= 7 ? launch_short_s<Cfg128x128>(a, G, stream) : launch_short_s<Cfg128x64>(a, G, stream);
@@ -840,6 +844,30 @@ hipError_t launch_mfma8_cfg(const StepArgs& a0, int G, hipStream_t stream, char*
         case MFMA8_256x64: return launch_cfg<Cfg256x64>(a, G, stream, scratch, scratch_per_plane);
         default: return launch_cfg<Cfg128x64>(a, G, stream, scratch, scratch_per_plane);
     }
+}
+
+// K of at most 32 entries and a B side of 16 or 32 rows: bound by reading A and
+// writing C, which the streaming kernel did a byte per lane (2^21 x 2^4 outputs
+// over K = 32: 80 us a plane, over K = 16: 78 us; here 22 and 20). At least
+// one tile of 512 rows; fewer B rows would leave most of a block's columns
+// empty.
+bool short8_eligible(const StepArgs& a) {
+    return a.s >= 0 && a.s <= 5 && (a.fB == 4 || a.fB == 5) && a.fA >= 9 && a.fA + a.fB <= 45;
+}
+
+hipError_t launch_short8(const StepArgs& a0, int G, hipStream_t stream, Profiler* prof, double step_bytes,
+                         double step_macs) {
+    if (!short8_eligible(a0)) return hipErrorInvalidValue;
+    StepArgs a = a0;
+    const bool ex = (a.maskB & 3) == 3;  // as in launch_mfma8_cfg
+    if (ex) exchange(a);
+    prof->before(stream);
+    const hipError_t e = a0.fB == 4 ? (ex ? launch_short_s<Cfg16x256>(a, G, stream)
+                                          : launch_short_s<Cfg512x16>(a, G, stream))
+                                    : (ex ? launch_short_s<Cfg32x256>(a, G, stream)
+                                          : launch_short_s<Cfg512x32>(a, G, stream));
+    prof->after_raw(stream, KC_NARROW, step_bytes, step_macs);
+    return e;
 }
 
 hipError_t launch_mfma8(const StepArgs& a, int G, hipStream_t stream, Profiler* prof, double step_bytes,
