@@ -239,7 +239,7 @@ using Cfg256x128 = Cfg<256, 128, 8, 8, 2>;
 using Cfg128x128 = Cfg<128, 128, 8, 4, 2>;
 using Cfg256x64 = Cfg<256, 64, 4, 4, 4>;
 using Cfg128x64 = Cfg<128, 64, 4, 2, 4>;
-// short K only: few rows on one side
+// few rows on one side (K <= 32), or 256 of the other held in registers
 using Cfg512x16 = Cfg<512, 16, 4, 8, 1>;
 using Cfg512x32 = Cfg<512, 32, 4, 8, 2>;
 using Cfg64x256 = Cfg<64, 256, 4, 4, 4>;
@@ -513,6 +513,137 @@ __global__ __launch_bounds__(G::THREADS, 1) void k_mfma8(StepArgs a, Mfma8Extra 
     }
 }
 
+// K = 64 CH = 128 or 256 with 256 or more rows on both sides: one side's rows stay
+// in registers, the other's stream past. With K this short a tile of k_mfma8
+// spends most of its time outside its products, in an epilogue that no
+// products run beside (two waves per SIMD, both in the same phase) and in two
+// or three barriers: 256 x 256 tiles over K = 256 took 8.7 us, 2.7 of them products.
+// Here a work-group of four waves holds 256 resident rows, 64 per wave, as
+// fragments (16 CH registers per lane) and walks 2^lgL tiles of 64 streamed rows,
+// double-buffered whole in LDS (16 KiB each at K = 256) and shared by its waves.
+// Two such work-groups fit a CU (three at K = 128) and run freely, so that one's
+// epilogue lies beside another's products. Bound by writing C: rank 26 x 18 over
+// K = 2^8, 10 planes, 1486 -> 890 us (3.8 TB/s), 31 x 17, 2 planes, 4460 -> 3550, 23 x 19,
+// 10 planes, 328 -> 267; K = 2^7: 24 x 17, 8 planes, 403 -> 295 us (4.1 TB/s). Tiles of
+// 128 streamed rows (255 registers) and three work-groups at K = 256 (168) spilled
+// fragments: 1313 us for the first. A third buffer gave nothing.
+//
+// RES_A: A's rows are resident (256 x 64 tiles), else B's (64 x 256). Items are
+// (plane, run of streamed tiles, resident tile); with `spread` the resident
+// tiles of one run go to one XCD's work-groups.
+constexpr uint32_t kCUs = 256;
+// work-groups per CU: 187 registers at K = 256, 151 at K = 128
+template <int CH>
+constexpr int kRowsPerCU = CH == 4 ? 2 : 3;
+template <class G, bool RES_A, int CH, int RED, bool PAIR>
+__global__ __launch_bounds__(G::THREADS, kRowsPerCU<CH>) void k_mfma8_rows(StepArgs a, Mfma8Extra ex,
+                                                                            uint32_t items, int lgL, int spread) {
+    constexpr int RA = G::RA, CB = G::CB;
+    using Pc = Piece<RA, CB>;
+    constexpr int STORES = Pc::N * Pc::NT;
+    constexpr int ROW = 64 * CH, SLOTS = 4 * CH;  // LDS row bytes, slots of 16 bytes
+    constexpr int NS = 4, NR = 4;                 // streamed and resident blocks of a wave
+    static_assert(G::NW == 4 && (RES_A ? CB : RA) == NS && (RES_A ? RA : CB) == NR, "one wave: 64 resident rows");
+    constexpr int BUF = 64 * ROW, LD = BUF / 4096;  // loads per wave and tile
+    __shared__ __align__(1024) uint8_t lds[2 * BUF + 4 * Pc::BYTES];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 15, q = lane >> 4;
+    const int lgS = (RES_A ? a.fB : a.fA) - 6, lgR = (RES_A ? a.fA : a.fB) - 8, lgSeg = lgS - lgL;
+    const uint64_t hiS = RES_A ? ex.hiB : ex.hiA, hiR = RES_A ? ex.hiA : ex.hiB;
+    const uint64_t oneS = hiS & (~hiS + 1);
+    const uint64_t waveC = pdep64(uint64_t(64 * w), RES_A ? a.maskA : a.maskB);
+    uint8_t* const wstage = lds + 2 * BUF + w * Pc::BYTES;
+    // lane l of wave w, instruction i fills physical slot l % SLOTS of row
+    // r = (64 / SLOTS) (4 i + w) + l / SLOTS: logical slot (l % SLOTS) ^ (r % SLOTS)
+    constexpr int RPI = 64 / SLOTS;
+    const int lr = RPI * w + lane / SLOTS;
+    const uint32_t voff = uint32_t(lr * ROW + 16 * ((lane % SLOTS) ^ (lr % SLOTS)));
+    // fragment of chunk c: row fr at logical slot 4 c + q, i.e. rd ^ 64 c
+    const uint32_t rd = uint32_t(fr * ROW + 16 * (q ^ (fr % SLOTS)));
+    constexpr int32_t Z = RED == RED_BIAS ? kBiasBits : 0;
+    const uint32_t tiles = 1u << lgL;
+
+    for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
+        const uint32_t j = spread ? it >> 3 : it;
+        const uint32_t r = j & ((1u << lgR) - 1);
+        const uint32_t sg = spread ? ((j >> lgR) << 3) | (it & 7) : j >> lgR;
+        const uint32_t g = sg >> lgSeg, s0 = (sg & ((1u << lgSeg) - 1)) << lgL;
+        const int8_t* const pS = (RES_A ? static_cast<const int8_t*>(a.B) + g * a.strideB
+                                        : static_cast<const int8_t*>(a.A) + g * a.strideA) +
+                                 uint64_t(s0) * BUF;
+        const int8_t* const pR = (RES_A ? static_cast<const int8_t*>(a.A) + g * a.strideA
+                                        : static_cast<const int8_t*>(a.B) + g * a.strideB) +
+                                 (uint64_t(r) * 256 + uint64_t(64 * w)) * ROW;
+        int8_t* const C = static_cast<int8_t*>(a.C) + g * a.strideC;
+        const ModSmall ms{int32_t(a.p[g]), a.r2[g], a.r16[g], a.pinv[g]};
+        const auto fetch = [&](uint32_t t) {
+            uint32_t vo = voff;
+            __asm__ volatile("" : "+v"(vo));
+            const int8_t* base = pS + uint64_t(t < tiles ? t : tiles - 1) * BUF;
+            uint8_t* dst = lds + (t & 1) * BUF + w * 1024;
+#pragma unroll
+            for (int i = 0; i < LD; ++i)
+                __builtin_amdgcn_global_load_lds(base + i * 4096 + vo, (lds_ptr_t)(dst + i * 4096), 16, 0, 0);
+        };
+        // every wave has read its last fragments of the item before, and the
+        // loads behind that run's end have landed
+        chunk_barrier<STORES>();
+        fetch(0);
+        fetch(1);
+        v4i res[CH][NR];
+        uint32_t ro = uint32_t(fr * ROW + 16 * q);
+        __asm__ volatile("" : "+v"(ro));
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int b = 0; b < NR; ++b) res[c][b] = *reinterpret_cast<const v4i*>(pR + (16 * b * ROW + 64 * c) + ro);
+        __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
+        uint64_t depS = pdep_from(s0, hiS);
+        const uint64_t baseR = pdep_from(r, hiR) | waveC;
+        for (uint32_t t = 0; t < tiles; ++t) {
+            // tile t has landed; younger: the stores of tile t - 2, the loads of
+            // tile t + 1, the stores of tile t - 1 (fewer operations only behind
+            // the drain above, which covers tiles 0 and 1)
+            chunk_barrier<LD + 2 * STORES>();
+            v4i acc[RA][CB], fs[NS];
+            uint32_t at = rd + (t & 1) * uint32_t(BUF);
+            __asm__ volatile("" : "+v"(at));
+#pragma unroll
+            for (int b = 0; b < NS; ++b) fs[b] = *reinterpret_cast<const v4i*>(lds + at + b * 16 * ROW);
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                if (c + 1 < CH)
+                    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(63));  // as in k_mfma8
+                else {
+                    // every fragment is in registers: the buffer takes tile
+                    // t + 2 (the last tile again behind the run's end, where
+                    // the count of operations has to stay the same)
+                    chunk_barrier<63>();
+                    fetch(t + 2);
+                }
+                uint32_t nx = rd;
+                __asm__ volatile("" : "+v"(nx));
+                nx = (nx ^ uint32_t(64 * (c + 1))) + (t & 1) * uint32_t(BUF);
+#pragma unroll
+                for (int b = 0; b < NS; ++b) {
+#pragma unroll
+                    for (int x = 0; x < NR; ++x) {
+                        v4i& d = acc[RES_A ? x : b][RES_A ? b : x];
+                        const v4i z = c == 0 ? v4i{Z, Z, Z, Z} : d;
+                        d = RES_A ? __builtin_amdgcn_mfma_i32_16x16x64_i8(res[c][x], fs[b], z, 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_i32_16x16x64_i8(fs[b], res[c][x], z, 0, 0, 0);
+                    }
+                    if (c + 1 < CH) fs[b] = *reinterpret_cast<const v4i*>(lds + nx + b * 16 * ROW);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            store_staged<RA, CB, RED, PAIR>(acc, C, depS | baseR, ex, ms, lane, wstage);
+            depS = ((depS | ~hiS) + oneS) & hiS;
+        }
+    }
+}
+
 // split-K: sum the partial residues of every K range and scatter into C; a
 // thread takes 16 consecutive A indices, whose C offsets differ by the same
 // 16 deposits everywhere (one output and two bit deposits per thread made
@@ -722,7 +853,7 @@ Mfma8Extra extra_of(const StepArgs& a) {
 // A grid that fills the GPU once: the work-groups walk the tiles of every
 // plane, so that only their first tile waits for its first stages unhidden
 // (launched per plane with 1024 work-groups, a group had 4 to 32 tiles).
-constexpr uint32_t kCUs = 256;
+
 template <class Gm, int NST, int RED>
 void launch_nst(const StepArgs& a, const Mfma8Extra& ex, int G, uint64_t T, int splits, int8_t* part,
                int64_t scratch_per_plane, hipStream_t stream) {
@@ -794,6 +925,24 @@ hipError_t launch_short_s(const StepArgs& a, int G, hipStream_t stream) {
     }
 }
 
+// Work-groups that hold rows in registers run in pairs on every CU; a run is
+// as long as leaves four of them for each.
+template <class Gm, bool RES_A, int CH, int RED>
+hipError_t launch_rows(const StepArgs& a, int G, hipStream_t stream) {
+    const int lgS = (RES_A ? a.fB : a.fA) - 6, lgR = (RES_A ? a.fA : a.fB) - 8;
+    int lgL = std::min(lgS, 6);
+    while (lgL > 2 && (uint64_t(G) << (lgS - lgL + lgR)) < 4 * kRowsPerCU<CH> * kCUs) --lgL;
+    const uint32_t runs = uint32_t(G) << (lgS - lgL), items = runs << lgR;
+    const Mfma8Extra ex = extra_of<Gm>(a);
+    const dim3 grid(std::min<uint32_t>(items, kRowsPerCU<CH> * kCUs)), block(Gm::THREADS);
+    const int spread = runs % 8 == 0;
+    if (ex.mode == 0)
+        hipLaunchKernelGGL((k_mfma8_rows<Gm, RES_A, CH, RED, false>), grid, block, 0, stream, a, ex, items, lgL, spread);
+    else
+        hipLaunchKernelGGL((k_mfma8_rows<Gm, RES_A, CH, RED, true>), grid, block, 0, stream, a, ex, items, lgL, spread);
+    return hipGetLastError();
+}
+
 // A as B and B as A.
 void exchange(StepArgs& a) {
     std::swap(a.A, a.B);
@@ -846,6 +995,28 @@ hipError_t launch_mfma8_cfg(const StepArgs& a0, int G, hipStream_t stream, char*
     }
 }
 
+// From 2048 tiles of 64 x 256 on; below, a work-group has too few tiles per resident
+// fragment load (K = 256: 9 planes of 2^20 outputs 14.1 us against 13.3 in k_mfma8, 2^22
+// 27.5 against 28.2, 2^24 68 against 70; K = 128: 2^22 21.5 against 23.4, 2^24 48 against
+// 54).
+bool rows8_eligible(const StepArgs& a, int G) {
+    const int hi = std::max(a.fA, a.fB), lo = std::min(a.fA, a.fB);
+    return (a.s == 7 || a.s == 8) && lo >= 8 && hi + lo <= 45 && (uint64_t(G) << (hi - 6 + lo - 8)) >= 2048;
+}
+
+hipError_t launch_rows8(const StepArgs& a0, int G, hipStream_t stream) {
+    StepArgs a = a0;
+    if (a.fB > a.fA) exchange(a);
+    // the larger side streams; C's two lowest bits are A's or one of each
+    if ((a.maskB & 3) == 3) {
+        exchange(a);
+        return a.s == 8 ? launch_rows<Cfg256x64, true, 4, RED_BIAS>(a, G, stream)
+                        : launch_rows<Cfg256x64, true, 2, RED_BIAS>(a, G, stream);
+    }
+    return a.s == 8 ? launch_rows<Cfg64x256, false, 4, RED_BIAS>(a, G, stream)
+                    : launch_rows<Cfg64x256, false, 2, RED_BIAS>(a, G, stream);
+}
+
 // K of at most 32 entries and a B side of 16 or 32 rows: bound by reading A and
 // writing C, which the streaming kernel did a byte per lane (2^21 x 2^4 outputs
 // over K = 32: 80 us a plane, over K = 16: 78 us; here 22 and 20). At least
@@ -876,7 +1047,8 @@ hipError_t launch_mfma8(const StepArgs& a, int G, hipStream_t stream, Profiler* 
     prof->before(stream);
     // the autotuner's measured tile shape for the nearest tuned shape, else the rule
     const int cfg = a.s >= 6 ? tuned_choice(TK_MFMA8, EL_I8, a.fA, a.fB, a.s) : MFMA8_RULE;
-    const hipError_t e = launch_mfma8_cfg(a, G, stream, scratch, scratch_per_plane, cfg);
+    const hipError_t e = rows8_eligible(a, G) ? launch_rows8(a, G, stream)
+                                              : launch_mfma8_cfg(a, G, stream, scratch, scratch_per_plane, cfg);
     prof->after_raw(stream, KC_MFMA, step_bytes, step_macs);
     return e;
 }
