@@ -908,7 +908,13 @@ hipError_t launch_cfg(const StepArgs& a, int G, hipStream_t stream, char* scratc
 template <class Gm, int S>
 hipError_t launch_short(const StepArgs& a, int G, hipStream_t stream) {
     const uint64_t T = (uint64_t(1) << (a.fA - Gm::LGM)) * (uint64_t(1) << (a.fB - Gm::LGN));
-    dim3 grid(uint32_t(std::min<uint64_t>(T, 2048)), 1, G);
+    // A work-group walks up to eight tiles, so that all but the first tile's
+    // loads run beside products and stores, as long as 2048 work-groups remain
+    // (rank 16 x 16 over K = 16, 8 planes: one tile each 57 us, four 44; rank 21 x 14
+    // over K = 32 126, 91). Where there are more the old bound of 2048 a plane
+    // holds: rank 17 x 15 over K = 4 631 us, 650 with 2048 in all.
+    const uint64_t walk = std::max<uint64_t>({T / 8, 2048u / uint64_t(G), 1});
+    dim3 grid(uint32_t(std::min<uint64_t>({T, walk, 2048})), 1, G);
     hipLaunchKernelGGL((k_mfma8_short<Gm, S>), grid, dim3(Gm::THREADS), 0, stream, a, extra_of<Gm>(a));
     return hipGetLastError();
 }
