@@ -837,7 +837,14 @@ hipError_t launch_mfma(const StepArgs& a, int G, hipStream_t stream, Profiler* p
     }
     uint32_t* part = reinterpret_cast<uint32_t*>(scratch);
     const int64_t part_stride = scratch_per_plane / 4;
-    dim3 grid(uint32_t(std::min<uint64_t>(T, 1024)), uint32_t(splits), G);
+    // One work-group fits a CU; each walks several tiles where there are more
+    // than 1024 of them, so that a tile's loads run beside the last one's products
+    // and stores. A power of two a plane: equal shares (rank 16 x 19 over K = 64, 6
+    // planes of 512 tiles: 121 us with a work-group per tile, 104 with 256 a plane, 93
+    // with 128, 92 with 42; rank 23 x 23 over K = 2^11: 719, 675, 656, 688).
+    uint64_t groups = 1;
+    while (groups < T && groups * 2 * uint64_t(G) * uint64_t(splits) <= 1024) groups *= 2;
+    dim3 grid(uint32_t(groups), uint32_t(splits), G);
     prof->before(stream);
     if (sq)
         hipLaunchKernelGGL(k_mfma_sq, grid, dim3(kThreads), 0, stream, a, ex, splits, part, part_stride);
