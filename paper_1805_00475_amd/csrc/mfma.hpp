@@ -51,7 +51,7 @@ int mfma8_rule_cfg(const StepArgs& a);
 // measurement launches).
 hipError_t launch_mfma8_cfg(const StepArgs& a, int G, hipStream_t stream, char* scratch, int64_t scratch_per_plane,
                             int cfg);
-// K of 128 or 256, one side's rows held in registers (mfma8.hip).
+// K of 128 to 512, one side's rows held in registers (mfma8.hip).
 hipError_t launch_rows8(const StepArgs& a, int G, hipStream_t stream);
 bool rows8_eligible(const StepArgs& a, int G);
 // Narrow int8 matrix-core step (narrow8.hip): B side of at most 64 rows,

@@ -513,7 +513,7 @@ __global__ __launch_bounds__(G::THREADS, 1) void k_mfma8(StepArgs a, Mfma8Extra 
     }
 }
 
-// K = 64 CH = 128 or 256 with 256 or more rows on both sides: one side's rows stay
+// K = 64 CH = 128, 256 or 512 with 256 or more rows on both sides: one side's rows stay
 // in registers, the other's stream past. With K this short a tile of k_mfma8
 // spends most of its time outside its products, in an epilogue that no
 // products run beside (two waves per SIMD, both in the same phase) and in two
@@ -521,20 +521,21 @@ __global__ __launch_bounds__(G::THREADS, 1) void k_mfma8(StepArgs a, Mfma8Extra 
 // Here a work-group of four waves holds 256 resident rows, 64 per wave, as
 // fragments (16 CH registers per lane) and walks 2^lgL tiles of 64 streamed rows,
 // double-buffered whole in LDS (16 KiB each at K = 256) and shared by its waves.
-// Two such work-groups fit a CU (three at K = 128) and run freely, so that one's
-// epilogue lies beside another's products. Bound by writing C: rank 26 x 18 over
-// K = 2^8, 10 planes, 1486 -> 890 us (3.8 TB/s), 31 x 17, 2 planes, 4460 -> 3550, 23 x 19,
-// 10 planes, 328 -> 267; K = 2^7: 24 x 17, 8 planes, 403 -> 295 us (4.1 TB/s). Tiles of
-// 128 streamed rows (255 registers) and three work-groups at K = 256 (168) spilled
-// fragments: 1313 us for the first. A third buffer gave nothing.
+// Two such work-groups fit a CU (80 KiB each at K = 512; three at K = 128) and run
+// freely, so that one's epilogue lies beside another's products. Bound by
+// writing C: K = 2^8, rank 26 x 18, 10 planes, 1486 -> 890 us (3.8 TB/s), 31 x 17, 2 planes,
+// 4460 -> 3550, 23 x 19, 10 planes, 328 -> 267; K = 2^7: 24 x 17, 8 planes, 403 -> 295 us
+// (4.1 TB/s); K = 2^9: 26 x 19, 8 planes, 769 -> 545. Tiles of 128 streamed rows (255
+// registers) and three work-groups at K = 256 (168) spilled fragments: 1313 us for
+// the first. A third buffer gave nothing.
 //
 // RES_A: A's rows are resident (256 x 64 tiles), else B's (64 x 256). Items are
 // (plane, run of streamed tiles, resident tile); with `spread` the resident
 // tiles of one run go to one XCD's work-groups.
 constexpr uint32_t kCUs = 256;
-// work-groups per CU: 187 registers at K = 256, 151 at K = 128
+// work-groups per CU: 253 registers at K = 512, 193 at K = 256, 157 at K = 128
 template <int CH>
-constexpr int kRowsPerCU = CH == 4 ? 2 : 3;
+constexpr int kRowsPerCU = CH >= 4 ? 2 : 3;
 template <class G, bool RES_A, int CH, int RED, bool PAIR>
 __global__ __launch_bounds__(G::THREADS, kRowsPerCU<CH>) void k_mfma8_rows(StepArgs a, Mfma8Extra ex,
                                                                             uint32_t items, int lgL, int spread) {
@@ -542,6 +543,7 @@ __global__ __launch_bounds__(G::THREADS, kRowsPerCU<CH>) void k_mfma8_rows(StepA
     using Pc = Piece<RA, CB>;
     constexpr int STORES = Pc::N * Pc::NT;
     constexpr int ROW = 64 * CH, SLOTS = 4 * CH;  // LDS row bytes, slots of 16 bytes
+    constexpr int SW = CH == 8 ? 8 : SLOTS;
     constexpr int NS = 4, NR = 4;                 // streamed and resident blocks of a wave
     static_assert(G::NW == 4 && (RES_A ? CB : RA) == NS && (RES_A ? RA : CB) == NR, "one wave: 64 resident rows");
     constexpr int BUF = 64 * ROW, LD = BUF / 4096;  // loads per wave and tile
@@ -555,12 +557,13 @@ __global__ __launch_bounds__(G::THREADS, kRowsPerCU<CH>) void k_mfma8_rows(StepA
     const uint64_t waveC = pdep64(uint64_t(64 * w), RES_A ? a.maskA : a.maskB);
     uint8_t* const wstage = lds + 2 * BUF + w * Pc::BYTES;
     // lane l of wave w, instruction i fills physical slot l % SLOTS of row
-    // r = (64 / SLOTS) (4 i + w) + l / SLOTS: logical slot (l % SLOTS) ^ (r % SLOTS)
+    // r = (64 / SLOTS) (4 i + w) + l / SLOTS: logical slot (l % SLOTS) ^ (r % SW) (the
+    // work-group's instruction covers a multiple of SW rows: i does not matter)
     constexpr int RPI = 64 / SLOTS;
     const int lr = RPI * w + lane / SLOTS;
-    const uint32_t voff = uint32_t(lr * ROW + 16 * ((lane % SLOTS) ^ (lr % SLOTS)));
+    const uint32_t voff = uint32_t(lr * ROW + 16 * ((lane % SLOTS) ^ (lr % SW)));
     // fragment of chunk c: row fr at logical slot 4 c + q, i.e. rd ^ 64 c
-    const uint32_t rd = uint32_t(fr * ROW + 16 * (q ^ (fr % SLOTS)));
+    const uint32_t rd = uint32_t(fr * ROW + 16 * (q ^ (fr % SW)));
     constexpr int32_t Z = RED == RED_BIAS ? kBiasBits : 0;
     const uint32_t tiles = 1u << lgL;
 
@@ -943,7 +946,8 @@ hipError_t launch_rows(const StepArgs& a, int G, hipStream_t stream) {
     const dim3 grid(std::min<uint32_t>(items, kRowsPerCU<CH> * kCUs)), block(Gm::THREADS);
     const int spread = runs % 8 == 0;
     if (ex.mode == 0)
-        hipLaunchKernelGGL((k_mfma8_rows<Gm, RES_A, CH, RED, false>), grid, block, 0, stream, a, ex, items, lgL, spread);
+        hipLaunchKernelGGL((k_mfma8_rows<Gm, RES_A, CH, RED, false>), grid, block, 0, stream, a, ex, items, lgL,
+                           spread);
     else
         hipLaunchKernelGGL((k_mfma8_rows<Gm, RES_A, CH, RED, true>), grid, block, 0, stream, a, ex, items, lgL, spread);
     return hipGetLastError();
@@ -1004,10 +1008,12 @@ hipError_t launch_mfma8_cfg(const StepArgs& a0, int G, hipStream_t stream, char*
 // From 2048 tiles of 64 x 256 on; below, a work-group has too few tiles per resident
 // fragment load (K = 256: 9 planes of 2^20 outputs 14.1 us against 13.3 in k_mfma8, 2^22
 // 27.5 against 28.2, 2^24 68 against 70; K = 128: 2^22 21.5 against 23.4, 2^24 48 against
-// 54).
+// 54). At K = 512 from 16384 on (9 planes of 2^24 113 against 103, 8 of 2^25 172 against 186, of
+// 2^27 547 against 715).
 bool rows8_eligible(const StepArgs& a, int G) {
     const int hi = std::max(a.fA, a.fB), lo = std::min(a.fA, a.fB);
-    return (a.s == 7 || a.s == 8) && lo >= 8 && hi + lo <= 45 && (uint64_t(G) << (hi - 6 + lo - 8)) >= 2048;
+    return a.s >= 7 && a.s <= 9 && lo >= 8 && hi + lo <= 45 &&
+           (uint64_t(G) << (hi - 6 + lo - 8)) >= (a.s == 9 ? 16384 : 2048);
 }
 
 hipError_t launch_rows8(const StepArgs& a0, int G, hipStream_t stream) {
@@ -1016,11 +1022,13 @@ hipError_t launch_rows8(const StepArgs& a0, int G, hipStream_t stream) {
     // the larger side streams; C's two lowest bits are A's or one of each
     if ((a.maskB & 3) == 3) {
         exchange(a);
-        return a.s == 8 ? launch_rows<Cfg256x64, true, 4, RED_BIAS>(a, G, stream)
-                        : launch_rows<Cfg256x64, true, 2, RED_BIAS>(a, G, stream);
+        return a.s == 9   ? launch_rows<Cfg256x64, true, 8, RED_PLAIN>(a, G, stream)
+               : a.s == 8 ? launch_rows<Cfg256x64, true, 4, RED_BIAS>(a, G, stream)
+                          : launch_rows<Cfg256x64, true, 2, RED_BIAS>(a, G, stream);
     }
-    return a.s == 8 ? launch_rows<Cfg64x256, false, 4, RED_BIAS>(a, G, stream)
-                    : launch_rows<Cfg64x256, false, 2, RED_BIAS>(a, G, stream);
+    return a.s == 9   ? launch_rows<Cfg64x256, false, 8, RED_PLAIN>(a, G, stream)
+           : a.s == 8 ? launch_rows<Cfg64x256, false, 4, RED_BIAS>(a, G, stream)
+                      : launch_rows<Cfg64x256, false, 2, RED_BIAS>(a, G, stream);
 }
 
 // K of at most 32 entries and a B side of 16 or 32 rows: bound by reading A and

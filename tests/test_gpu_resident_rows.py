@@ -1,4 +1,4 @@
-"""Steps over 128 and 256 shared entries that keep one side's rows in registers,
+"""Steps over 128 to 512 shared entries that keep one side's rows in registers,
 against exact products in double precision: every order of C's two lowest bits
 (either side resident, words paired or not), the fewest rows on either side,
 runs of one and of several tiles."""
@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("low", ["AA", "AB", "BA", "BB"])
-@pytest.mark.parametrize("fA,fB", [(17, 8), (13, 12), (9, 16)])
-@pytest.mark.parametrize("s", [7, 8])
+@pytest.mark.parametrize("fA,fB,s", [(17, 8, 7), (13, 12, 7), (9, 16, 7), (17, 8, 8), (13, 12, 8), (9, 16, 8),
+                                     (19, 9, 9)])
 def test_resident_rows(fA, fB, s, low):
     rng = np.random.default_rng(fA * 100 + s)
     m = 255 if low != "BA" else 254
@@ -29,7 +29,8 @@ def test_resident_rows(fA, fB, s, low):
     dA = _deposit(np.arange(1 << fA), maskA)
     dB = _deposit(np.arange(1 << fB), ((1 << (fA + fB)) - 1) ^ maskA)
     Bt = B.astype(np.float64).T
-    for r0 in range(0, 1 << fA, 1 << 12):
+    blocks = range(0, 1 << fA, 1 << 12)
+    for r0 in blocks if s < 9 else (0, 13 << 12, 64 << 12, (1 << fA) - (1 << 12)):
         rows = slice(r0, r0 + (1 << 12))
         want = np.fmod(A[rows].astype(np.float64) @ Bt, m)
         assert np.array_equal(C[dA[rows, None] | dB[None]], want)
