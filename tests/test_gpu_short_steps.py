@@ -18,7 +18,7 @@ def _deposit(x, mask):
     return out
 
 
-def _run(fA, fB, s, low, m, kind, seed):
+def _run(fA, fB, s, low, m, kind, seed, kernel="auto"):
     """low: the sides of C's lowest bits, from bit 0 on; the rest alternate."""
     rng = np.random.default_rng(seed)
     left, maskA = {"A": fA, "B": fB}, 0
@@ -35,7 +35,7 @@ def _run(fA, fB, s, low, m, kind, seed):
         A = rng.integers(0, m, size=1 << (fA + s)).astype(np.uint32)
         B = rng.integers(0, m, size=1 << (fB + s)).astype(np.uint32)
     print("[gpu case]", fA, fB, s, low, m, kind, flush=True)
-    C = tn.step(A, fA + s, B, fB + s, s, maskA, prime=m)
+    C = tn.step(A, fA + s, B, fB + s, s, maskA, prime=m, kernel=kernel)
     want = A.reshape(-1, 1 << s).astype(np.int64) @ B.reshape(-1, 1 << s).astype(np.int64).T % m
     cmask = (1 << (fA + fB)) - 1
     at = _deposit(np.arange(1 << fA), maskA)[:, None] | _deposit(np.arange(1 << fB), cmask ^ maskA)[None]
@@ -56,3 +56,23 @@ def test_few_rows_small_moduli(fB, s, low):
 def test_streaming_walks(fA, fB, s, m):
     for low in ("AAAA", "BBBB", "AB"):
         _run(fA, fB, s, low, m, "max" if low == "AB" else "uniform", fA + fB)
+
+
+@pytest.mark.parametrize("m", [255, 65267])
+@pytest.mark.parametrize("s", [0, 1, 2, 3, 4, 5, 6, 7, 16, 17, 18])
+def test_generic_row_lengths(s, m):
+    # rows of less than one vector, of several, and of several exact ranges
+    _run(3, 2, s, "AB", m, "uniform", s, "generic")
+    _run(2, 1, s, "BA", m, "max", s, "generic")
+
+
+@pytest.mark.parametrize("s", [0, 1, 2, 5, 17])
+def test_generic_row_lengths_u64(s):
+    rng = np.random.default_rng(s)
+    A = rng.integers(0, 1 << 62, size=4 << s, dtype=np.uint64)
+    B = rng.integers(0, 1 << 62, size=2 << s, dtype=np.uint64)
+    C = tn.step(A, s + 2, B, s + 1, s, 0b011, kernel="generic")
+    a, b = A.reshape(4, -1), B.reshape(2, -1)
+    for xa in range(4):
+        for xb in range(2):
+            assert int(C[xa | xb << 2]) == sum(int(v) for v in a[xa] * b[xb]) % (1 << 64)
