@@ -12,7 +12,7 @@
 //
 // Measured, 256 mixed instances of 30 to 120 variables (greedy order): 55 ms
 // with a wave kernel per level of small steps (34 MB of tile descriptors built and
-// copied per call) and one stream, 24 ms now, of which 20 are the host threads'
+// copied per call) and one stream, 23 ms now, of which 20 are the host threads'
 // building and ordering.
 #include <hip/hip_runtime.h>
 

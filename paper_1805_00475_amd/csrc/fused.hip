@@ -9,9 +9,12 @@
 // is its depth: about 10 levels of a barrier, a step's index gathers and its
 // sum, each a few LDS latencies; so programs are kept to the work at which a
 // step's sums would take longer than its own launch. Measured, one count with
-// its plan in hand: vertex cover n = 60 (149 steps, 64-bit counts) 620 -> 69
-// us, n = 120 (10 planes) 1161 -> 98 us, hard-core n = 100 (349 steps, 69
-// primes) 7.0 -> 0.53 ms; the launch itself takes 11-23 us.
+// its plan in hand, the narrow and generic kernels of its larger steps
+// included: vertex cover n = 60 (149 steps, 64-bit counts) 620 -> 50 us, n = 120
+// (9 planes) 1161 -> 97 us, hard-core n = 100 (349 steps, 66 primes) 7.0 -> 0.34 ms;
+// the launch itself takes 11-27 us. Measured and not used: a wave's next item
+// and step read ahead (n = 120: 22.6 -> 22.4 us of the launch), row offsets formed by an
+// unrolled pass over the bits instead of a loop over each mask (26.1).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
