@@ -38,8 +38,53 @@ constexpr int kPad = H + 4;    // LDS row of a 128-wide tile read four floats at
 constexpr int kRec = H * H + 2 * H + 1;  // gradients of W2, b2, w3, b3, packed as in the parameters
 static_assert(kOffB2 == kOffW2 + H * H && kOffW3 == kOffB2 + H && kOffB3 == kOffW3 + H, "packing");
 
-// acc[rb][cb] += rows of a tile (LDS, kPad floats each) times the wave's
-// fragments w[cb][kb]: lane l's floats j hold K index 16 kb + 4 (l / 16) + j
+// Place of unit u in a tile's row: the four units that a lane takes in one
+// 16-byte read, 16 kb + 4 j + l / 16 for j = 0..3, lie side by side.
+__device__ __forceinline__ constexpr int place(int u) { return (u & ~15) | ((u & 3) << 2) | ((u >> 2) & 3); }
+
+// The lane halves' (quarters') places of a and b exchanged: upper 32 lanes of a
+// with lower 32 of b (odd 16-lane rows of a with even ones of b).
+__device__ __forceinline__ void swap32(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap16(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+// Float j of lane row q (lane / 16) becomes float q of lane row j.
+__device__ __forceinline__ v4f transpose4(v4f x) {
+    float a = x[0], b = x[1], c = x[2], d = x[3];
+    swap32(a, c);
+    swap32(b, d);
+    swap16(a, b);
+    swap16(c, d);
+    return v4f{a, b, c, d};
+}
+// Sum over the wave, in every lane: v + v at lane ^ 32, then ^ 16, 8, 4, 2, 1 (what is
+// left repeats every 16, 8, 4 lanes, so that a rotation stands for the exchange).
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float v) {
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    float o = v;
+    swap32(v, o);
+    v += o;
+    o = v;
+    swap16(v, o);
+    v += o;
+    return add_dpp<0xb1>(add_dpp<0x4e>(add_dpp<0x124>(add_dpp<0x128>(v))));
+}
+
+// acc[rb][cb] += rows of a tile (LDS, kPad floats each, units at their places)
+// times the wave's fragments w[cb][kb]: lane l's float j holds unit
+// 16 kb + 4 j + l / 16, so that every sum takes the units in ascending order, as a
+// loop over them would: a pre-activation within rounding of zero has one sign
+// in every kernel that forms it, and the backward pass drops or keeps a whole
+// gradient by that sign.
 template <int RT>
 __device__ __forceinline__ void mul_tile(const float (&tile)[16 * RT][kPad], const v4f (&w)[2][8], int lane,
                                          v4f (&acc)[RT][2]) {
@@ -62,8 +107,8 @@ template <int RT>
 __global__ __launch_bounds__(kThreads) void k_forward(const float* P, const float* X, int64_t n, float* H1, float* H2,
                                                       float* y) {
     __shared__ __align__(16) float t1[16 * RT][kPad];
+    __shared__ float t2[16 * RT][kPad];
     __shared__ float sx[16 * RT][F];
-    __shared__ float ys[16 * RT][4];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, fr = lane & 15, q = lane >> 4;
     const int j = t & (H - 1);
     float w1[F];
@@ -71,15 +116,16 @@ __global__ __launch_bounds__(kThreads) void k_forward(const float* P, const floa
     for (int k = 0; k < F; ++k) w1[k] = P[kOffW1 + j * F + k];
     const float b1 = P[kOffB1 + j];
     v4f wf[2][8];
-    float b2[2], w3[2];
+    float b2[2];
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
         const int col = 32 * w + 16 * cb + fr;
 #pragma unroll
-        for (int kb = 0; kb < 8; ++kb) wf[cb][kb] = *reinterpret_cast<const v4u*>(P + kOffW2 + col * H + 16 * kb + 4 * q);
+        for (int kb = 0; kb < 8; ++kb)
+            wf[cb][kb] = transpose4(*reinterpret_cast<const v4u*>(P + kOffW2 + col * H + 16 * kb + 4 * q));
         b2[cb] = P[kOffB2 + col];
-        w3[cb] = P[kOffW3 + col];
     }
+    const float w3[2] = {P[kOffW3 + lane], P[kOffW3 + lane + 64]}, b3 = P[kOffB3];
     const int64_t tiles = (n + 16 * RT - 1) / (16 * RT);
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const int64_t base = tile * (16 * RT);
@@ -97,7 +143,7 @@ __global__ __launch_bounds__(kThreads) void k_forward(const float* P, const floa
                 h = a > 0.0f ? a : 0.0f;
                 H1[i * H + j] = h;
             }
-            t1[r][j] = h;
+            t1[r][place(j)] = h;
         }
         __syncthreads();
         v4f acc[RT][2];
@@ -112,19 +158,24 @@ __global__ __launch_bounds__(kThreads) void k_forward(const float* P, const floa
             for (int v = 0; v < 4; ++v) {
                 const int r = 16 * rb + 4 * q + v;
                 const int64_t i = base + r;
-                float s = 0.0f;
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb) {
                     const float a = acc[rb][cb][v];
                     const float h = a > 0.0f ? a : 0.0f;
                     if (i < n) H2[i * H + 32 * w + 16 * cb + fr] = h;
-                    s += h * w3[cb];
+                    t2[r][32 * w + 16 * cb + fr] = h;
                 }
-                for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
-                if (fr == 0) ys[r][w] = s;
             }
         __syncthreads();
-        if (t < 16 * RT && base + t < n) y[base + t] = ((ys[t][0] + ys[t][1]) + (ys[t][2] + ys[t][3])) + P[kOffB3];
+        // layer 3: a wavefront per row, 4 RT of them side by side
+        float s3 = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4 * RT; ++r) {
+            const float a = wave_sum(w3[0] * t2[4 * r + w][lane] + w3[1] * t2[4 * r + w][lane + 64]);
+            s3 = lane == r ? a : s3;
+        }
+        const int64_t i = base + 4 * lane + w;
+        if (lane < 4 * RT && i < n) y[i] = s3 + b3;
     }
 }
 
@@ -312,7 +363,7 @@ __global__ __launch_bounds__(kThreads) void k_back1(const float* P, const float*
         for (int kb = 0; kb < 8; ++kb)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
-                wf[cb][kb][jj] = P[kOffW2 + (16 * kb + 4 * q + jj) * H + 32 * w + 16 * cb + fr];
+                wf[cb][kb][jj] = P[kOffW2 + (16 * kb + 4 * jj + q) * H + 32 * w + 16 * cb + fr];
     // thread t sums unit k = t % 128: features 0..4 and the bias, or 5..9
     const int k = t & (H - 1), half = t >> 7;
     float g[F / 2], gb = 0.0f;
@@ -323,11 +374,13 @@ __global__ __launch_bounds__(kThreads) void k_back1(const float* P, const float*
         const int64_t base = tile * (16 * RT);
         __syncthreads();
 #pragma unroll
-        for (int e = t; e < 16 * RT * (H / 4); e += kThreads) {
-            const int r = e / (H / 4), c = 4 * (e % (H / 4));
+        for (int u = 0; u < RT * 2; ++u) {
+            // two rows per wave: lane row q holds the 16-byte pieces q of the
+            // rows' groups of 16 units
+            const int r = 8 * u + 2 * w + (fr >> 3), c = 16 * (fr & 7) + 4 * q;
             v4f d = {0, 0, 0, 0};
             if (base + r < n) d = *reinterpret_cast<const v4u*>(dZ2 + (base + r) * H + c);
-            *reinterpret_cast<v4f*>(&t2[r][c]) = d;
+            *reinterpret_cast<v4f*>(&t2[r][c]) = transpose4(d);
         }
         for (int e = t; e < 16 * RT * F; e += kThreads) sx[e / F][e % F] = base + e / F < n ? X[base * F + e] : 0.0f;
         __syncthreads();

@@ -1,0 +1,61 @@
+"""The perceptron's sums over the 128 units take them in ascending order, one
+fused multiply-add each: h1, h2 and dz1 bit for bit against that order (a unit
+whose pre-activation is within rounding of zero keeps its sign, and with it a
+whole gradient entry), dz2 from its factors."""
+import numpy as np
+import pytest
+
+from oracle import mlp
+from paper_1805_00475_amd import tn
+
+pytestmark = pytest.mark.gpu
+
+
+def _fma(a, b, c):
+    """fp32 a b + c rounded once: the product is exact in double, the sum is
+    rounded there to odd (its last bit set where it is inexact), then to fp32."""
+    p, c = a.astype(np.float64) * b.astype(np.float64), c.astype(np.float64)
+    s = p + c
+    t = s - p
+    err = (p - (s - t)) + (c - t)
+    bits = s.view(np.int64).copy()
+    fix = (err != 0) & (bits & 1 == 0)
+    away = (err > 0) == (s > 0)
+    bits[fix] += np.where(away, 1, -1)[fix]
+    return bits.view(np.float64).astype(np.float32)
+
+
+def _chain(x, w, start):
+    """start[j] + sum over k ascending of x[i][k] w[k][j]"""
+    acc = np.broadcast_to(start, (x.shape[0], w.shape[1])).astype(np.float32)
+    for k in range(x.shape[1]):
+        acc = _fma(np.broadcast_to(x[:, k:k + 1], acc.shape), np.broadcast_to(w[k], acc.shape), acc)
+    return acc
+
+
+# around a tile of 16 rows, and of 32 from 4096 rows on
+@pytest.mark.parametrize("n", [1, 16, 17, 201, 4095, 4096, 4131])
+def test_sums_ascend(n):
+    import torch
+    print("[gpu case] mlp order", n, flush=True)
+    r = np.random.default_rng(n)
+    x = r.normal(0, 1, (n, mlp.F)).astype(np.float32)
+    p = mlp.init_params(n).astype(np.float32)
+    p += r.normal(0, 0.05, p.size).astype(np.float32)  # (biases too)
+    groups = max(1, n // 200)
+    g = np.linspace(0, n, groups + 1).astype(np.int32)
+    lab = np.zeros(n, np.uint8)
+    lab[g[:-1]] = 1
+    f = dict(dtype=torch.float32, device="cuda")
+    h1, h2, dz1, dz2 = (torch.empty(n, mlp.H, **f) for _ in range(4))
+    y, dy = (torch.empty(n, **f) for _ in range(2))
+    grad, loss = torch.empty(mlp.N_PARAMS, **f), torch.empty(1, **f)
+    dev = [torch.from_numpy(a).cuda() for a in (p, x, lab, g)]
+    tn.mlp_forward(dev[0], dev[1], h1, h2, y)
+    tn.mlp_backward(dev[0], dev[1], h1, h2, y, dev[2], dev[3], grad, dz2, dz1, dy, loss)
+    h1, h2, dz1, dz2, dy = (t.cpu().numpy() for t in (h1, h2, dz1, dz2, dy))
+    w1, b1, w2, b2, w3, _ = (np.asarray(a, dtype=np.float32) for a in mlp.unpack(p))
+    assert np.array_equal(h1, np.maximum(_chain(x, w1.T, b1), 0))
+    assert np.array_equal(h2, np.maximum(_chain(h1, w2.T, b2), 0))
+    assert np.array_equal(dz2, np.where(h2 > 0, dy[:, None] * w3, np.float32(0)))
+    assert np.array_equal(dz1, np.where(h1 > 0, _chain(dz2, w2, np.float32(0)), np.float32(0)))
