@@ -86,7 +86,7 @@ constexpr size_t kFlush = 64;
 constexpr int kChains = 4;
 // LDS classes of the programs: work-groups of 512 threads, four, two or one
 // of which fit a CU's 160 KB.
-constexpr uint32_t kLdsClass[3] = {40u << 10, 80u << 10, 160u << 10};
+constexpr uint32_t kLdsClass[3] = {40u << 10, 80u << 10, uint32_t(kMaxProgramLds)};
 
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 // where an instance's planes start in the workspace (large tensors are laid

@@ -15,12 +15,14 @@ namespace {
 struct Limits {
     int rank;        // largest tensor rank of a fused step
     int64_t work;    // largest work of a program (work_of)
-    int64_t elems;   // largest LDS use (entries)
+    int64_t elems;   // largest LDS use of its tensors (entries)
 };
 
 // A work-group does about 30 multiply-adds per clock on bytes and 4 on 64-bit
-// words, so these programs end within a few launch times; LDS is held to 96
-// KB (most programs take less than 12). Measured with half and twice the work:
+// words, so these programs end within a few launch times; a program's tensors
+// are held to 96 KB of LDS (most programs take less than 12), and with its text,
+// which a long chain of tiny steps makes the larger part, to what a work-group
+// may ask for. Measured with half and twice the work:
 // vertex cover n = 60 82 / 53 / 53 us (2^15, 2^17, 2^18), hard-core n = 100 534 /
 // 489 / 498 us (2^16 and rank 12, 2^17, 2^18), vertex cover n = 120 95 / 93 / 93
 // us (2^16, 2^17, 2^18).
@@ -34,6 +36,12 @@ Limits limits_of(int es) {
 // about eight more (index gathers, reduction, store).
 int64_t work_of(const Step& st) {
     return (int64_t(1) << (st.rA + st.rB - st.s)) + (int64_t(8) << st.rC);
+}
+
+// Items of a step (64 outputs each) and bytes of a program's text.
+int64_t items_of(int rank) { return int64_t(1) << std::max(rank - 6, 0); }
+int64_t text_bytes(int64_t steps, int64_t items, int64_t levels) {
+    return (steps * int64_t(sizeof(FuseStep)) + (items + levels + 1) * 4 + 15) / 16 * 16;
 }
 
 int64_t lds_size(int rank) { return std::max<int64_t>(16, int64_t(1) << rank); }
@@ -74,19 +82,41 @@ void build_exec(const Plan& plan, int es, Exec& ex) {
     // fused[k]: step k and everything below it fits one program
     std::vector<uint8_t> fused(size_t(n_steps), 0), inner(size_t(n_steps), 0);
     std::vector<int64_t> work(size_t(n_steps), 0);
+    // steps and items of step k and all below, and entries that are in LDS
+    // together at the end of the first level (its inputs, and its outputs other
+    // than k's): what a program takes at least (it has its root's levels). The
+    // layout below decides; without this a long formula laid out thousands of
+    // programs that could not fit, one step smaller each time (3000 unit clauses,
+    // bytes: 0.4 s).
+    struct Size {
+        int64_t steps, items, first;
+    };
+    std::vector<Size> size(size_t(n_steps), Size{});
     for (int32_t k = 0; k < n_steps; ++k) {
         const Step& st = plan.steps[size_t(k)];
         if (std::max({st.rA, st.rB, st.rC}) > lim.rank) continue;
         int64_t w = work_of(st);
+        Size z{1, items_of(st.rC), 0};
         bool ok = true;
         for (int32_t id : {st.a, st.b}) {
-            if (id < n_init) continue;
-            ok = ok && fused[size_t(id - n_init)];
-            w += work[size_t(id - n_init)];
+            if (id < n_init) {
+                z.first += lds_size(plan.rank[size_t(id)]);
+                continue;
+            }
+            const size_t c = size_t(id - n_init);
+            ok = ok && fused[c];
+            w += work[c];
+            const Step& below = plan.steps[c];
+            z = {z.steps + size[c].steps, z.items + size[c].items,
+                 z.first + size[c].first + (below.level == 1 ? lds_size(below.rC) : 0)};
         }
         if (!ok || w > lim.work) continue;
+        if (z.first > lim.elems ||
+            align_up(z.first * es, 16) + text_bytes(z.steps, z.items, st.level) > kMaxProgramLds)
+            continue;
         fused[size_t(k)] = 1;
         work[size_t(k)] = w;
+        size[size_t(k)] = z;
         for (int32_t id : {st.a, st.b})
             if (id >= n_init) inner[size_t(id - n_init)] = 1;
     }
@@ -141,7 +171,14 @@ void build_exec(const Plan& plan, int es, Exec& ex) {
                 lds.release(loff[size_t(st.b)], lds_size(st.rB));
             }
         }
-        if (lds.high > lim.elems) {
+        int64_t n_items = 0, n_levels = 0;
+        for (size_t j = 0; j < mine.size(); ++j) {
+            const Step& st = plan.steps[size_t(mine[j])];
+            n_items += items_of(st.rC);
+            n_levels += j == 0 || st.level != plan.steps[size_t(mine[j - 1])].level;
+        }
+        const int64_t text = text_bytes(int64_t(mine.size()), n_items, n_levels);
+        if (lds.high > lim.elems || align_up(lds.high * es, 16) + text > kMaxProgramLds) {
             const Step& st = plan.steps[size_t(r)];
             fused[size_t(r)] = 0;
             for (int32_t id : {st.a, st.b})
@@ -168,7 +205,7 @@ void build_exec(const Plan& plan, int es, Exec& ex) {
             fs.maskA = uint16_t(st.maskA);
             fs.sr = uint16_t(uint32_t(st.s) | (uint32_t(st.rC) << 8) | (k == r ? kFuseRoot : 0));
             ex.psteps.push_back(fs);
-            const uint32_t chunks = st.rC > 6 ? 1u << (st.rC - 6) : 1u;
+            const uint32_t chunks = uint32_t(items_of(st.rC));
             for (uint32_t c = 0; c < chunks; ++c) ex.pitems.push_back(uint32_t(j) | (c << 16));
             ex.prog_entries += std::ldexp(1.0, st.rA) + std::ldexp(1.0, st.rB) + std::ldexp(1.0, st.rC);
             ex.prog_macs += std::ldexp(1.0, st.rA + st.rB - st.s);
@@ -178,7 +215,7 @@ void build_exec(const Plan& plan, int es, Exec& ex) {
         pg.n_levels = uint32_t(ex.plevels.size() - level0 - 1);
         pg.n_init = uint32_t(n_entries);
         pg.final = plan.steps[size_t(r)].out == plan.root ? 1u : 0u;
-        pg.prog_bytes = uint32_t(align_up(int64_t(pg.n_steps) * 16 + (int64_t(pg.n_items) + pg.n_levels + 1) * 4, 16));
+        pg.prog_bytes = uint32_t(text);
         ex.pinit_first.push_back(int32_t(ex.pinit.size()));
         for (int32_t id : inits) {
             ex.pinit.push_back(id);

@@ -57,7 +57,9 @@ struct Exec {
     double prog_entries = 0, prog_macs = 0;  // algorithmic totals of the programs, one plane
 };
 
-// LDS of a program for es-byte entries: its tensors, then the program.
+// LDS of a program for es-byte entries: its tensors, then the program; at most
+// what a work-group may ask for on gfx950.
+constexpr int64_t kMaxProgramLds = int64_t(160) << 10;
 inline uint32_t lds_of(const FuseProg& pg, int es) {
     return (pg.lds_elems * uint32_t(es) + 15) / 16 * 16 + pg.prog_bytes;
 }
