@@ -230,7 +230,9 @@ tn_status tn_plan_verify(const tn_plan* plan);
 /* --------------------------------------------------------------- contract
  * Device workspace needed for a plan under opts (arith, n_primes,
  * prime_group, flags; workspace fields ignored). With prime_group = 0 the
- * answer is for one residue plane resident at a time. */
+ * answer is for one residue plane (or the 64-bit one) resident at a time, with
+ * k > 0 for k of them. It is enough for the faster of the library's two
+ * layouts; a call may also run in a little less. */
 tn_status tn_workspace_bytes(const tn_network* net, const tn_plan* plan,
                              const tn_contract_opts* opts, size_t* bytes);
 
@@ -254,7 +256,7 @@ tn_status tn_contract(const tn_network* net, const tn_plan* plan, const tn_contr
  * tn_contract, and the outputs are tn_contract's. Returns TN_ETOOBIG before
  * any device work when the plan's initial tensors, one residue plane's
  * arena and its scratch do not fit the array (tn_workspace_bytes with
- * prime_group = 0 gives the need), TN_EUNSUPPORTED with TN_FLAG_TIMING.
+ * prime_group = 0 is enough), TN_EUNSUPPORTED with TN_FLAG_TIMING.
  * Every call on one GPU uses that GPU's one array and leaves its contents
  * behind (nothing in it needs to start at zero): calls that overlap on one
  * GPU, from two threads or on two streams, race and must not be made. */

@@ -367,6 +367,7 @@ extern "C" tn_status tn_count_batch(const tn_formula* fs, int32_t n, tn_order_ki
         if (I.st != TN_OK) return;
         I.st = resolve(I.plan, opts, I.R);
         if (I.st != TN_OK) return;
+        const Resolved asked = I.R;
         if (Resolved rr; residue_route(I.plan, I.R, opts->flags, rr)) I.R = rr;
         I.P = I.R.u64 ? 1 : I.R.k;
         I.es = I.R.es();
@@ -393,9 +394,11 @@ extern "C" tn_status tn_count_batch(const tn_formula* fs, int32_t n, tn_order_ki
         const int64_t need = bytes_of(I);
         if (need > cap) {
             // too large to share the workspace: run alone, primes grouped as memory allows
+            // (and 64-bit counts by the route that suits the planes that fit)
             flush();
             std::vector<uint32_t> res;
             uint64_t v = 0;
+            I.R = asked;
             I.st = run_plan(I.net, I.plan, opts, I.R, res, &v);
             I.res = res;
             I.u64v = v;

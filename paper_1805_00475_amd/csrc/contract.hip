@@ -862,12 +862,35 @@ bool residue_route(const Plan& plan, const Resolved& R, int flags, Resolved& rr)
     return true;
 }
 
+// Planes of R that the workspace holds at a time, by either layout.
+static int64_t resident_planes(const Plan& plan, const Resolved& R, const tn_contract_opts* o) {
+    Exec own, plain;
+    plain_exec(plan, plain);
+    const int64_t ws = int64_t(o->workspace_bytes);
+    return std::min<int64_t>(std::max(layout_of(plan, *exec_of(plan, R, o->flags, own), R).planes(ws),
+                                      layout_of(plan, plain, R).planes(ws)),
+                             std::min(R.k, kMaxGroup));
+}
+
 tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,
                    std::vector<uint32_t>& residues, uint64_t* u64v, bool pinned) {
     Resolved rr;
     if (!o || !residue_route(plan, R, o->flags, rr)) return run_planes(net, plan, o, R, residues, u64v, pinned);
-    // a 64-bit plane's workspace holds several residue planes: the option to
-    // keep few of them resident is about that one plane
+    // Groups of planes, as many of them resident as fit (a 64-bit plane's
+    // workspace holds several: the option to keep few resident is about that
+    // one plane). Every group after the first costs its launches again, 0.06 to
+    // 0.1 ms, so that with few planes at a time the route has to save more: 5e7
+    // multiply-adds, 64-bit 0.127 ms against 0.088 / 0.144 / 0.203 in 1 / 2 / 3
+    // groups; 3e8, 0.372 against 0.109 / 0.187 / 0.265, 0.499 in 6; 1.2e9, 1.11 against
+    // 0.685 in 7.
+    const int64_t fit = resident_planes(plan, rr, o);
+    if (fit >= 1) {
+        const int64_t groups = (rr.k + fit - 1) / fit;
+        if (groups > 1 && plan.stats.macs < kResidueMacs + double(groups - 1) * kResidueGroupMacs) {
+            const tn_status st = run_planes(net, plan, o, R, residues, u64v, pinned);
+            if (st != TN_ETOOBIG) return st;
+        }
+    }
     tn_contract_opts ro = *o;
     ro.prime_group = 0;
     std::vector<uint32_t> res, limbs;
@@ -900,9 +923,12 @@ tn_status tn_workspace_bytes(const tn_network* net, const tn_plan* plan, const t
         int64_t need = std::max(layout_of(plan->plan, *ex, R).bytes(G), layout_of(plan->plan, plain, R).bytes(G));
         Resolved rr;
         if (residue_route(plan->plan, R, opts ? opts->flags : 0, rr)) {
+            // one residue plane takes less than the 64-bit one; planes
+            // asked to be resident together are the route's
             Exec rown;
             const Exec* rex = exec_of(plan->plan, rr, 0, rown);
-            need = std::max(need, layout_of(plan->plan, *rex, rr).bytes(std::min(rr.k, kMaxGroup)));
+            const int RG = opts && opts->prime_group > 0 ? std::min({opts->prime_group, rr.k, kMaxGroup}) : 1;
+            need = std::max(need, layout_of(plan->plan, *rex, rr).bytes(RG));
         }
         *bytes = size_t(need);
     } catch (const std::bad_alloc&) {

@@ -173,6 +173,8 @@ tn_status resolve(const Plan& plan, const tn_contract_opts* o, Resolved& r);
 // formulas, 64-bit against residues: 2e7 multiply-adds 0.128 / 0.116 ms, 3e7
 // 0.124 / 0.131 ms, 3e8 0.48 / 0.15 ms, 5e9 4.1 / 0.76 ms, 1.4e11 116.6 / 3.0 ms.
 constexpr double kResidueMacs = 33554432.0;  // 2^25
+// and per further group of planes where not all are resident (run_plan)
+constexpr double kResidueGroupMacs = 134217728.0;  // 2^27
 inline bool counts_by_residues(const Plan& plan) {
     return plan.count_bits <= 63 && plan.stats.macs >= kResidueMacs;
 }

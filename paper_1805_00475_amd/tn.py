@@ -367,6 +367,18 @@ def workspace_bytes(net: Network, plan: Plan, arith="auto", n_primes=0, prime_gr
     return b.value
 
 
+ROUTE_MACS = 2 ** 25   # multiply-adds from which 64-bit counts run in small moduli
+
+
+def _need(net: Network, plan: Plan, arith, n_primes, prime_group, flags) -> int:
+    """Workspace a count asks for: workspace_bytes, and for 64-bit counts that
+    run in small moduli all of those planes together (the size of about one
+    64-bit plane)."""
+    if prime_group == 0 and plan.stats["macs"] >= ROUTE_MACS and not moduli(plan, arith, n_primes, flags):
+        prime_group = 16
+    return workspace_bytes(net, plan, arith, n_primes, prime_group, flags)
+
+
 def _limbs_to_int(buf, n) -> int:
     v = 0
     for i in reversed(range(n)):
@@ -379,8 +391,7 @@ def contract(net: Network, plan: Plan, arith="auto", n_primes=0, workspace: Work
     """Run a plan; returns the residues list (RNS) or the exact int (U64)."""
     lib = load()
     ws = workspace or default_workspace()
-    need = workspace_bytes(net, plan, arith, n_primes, prime_group, flags)
-    ptr, nb = ws.get(max(need, max_bytes))
+    ptr, nb = ws.get(max(_need(net, plan, arith, n_primes, prime_group, flags), max_bytes))
     o = _opts(arith, n_primes, ptr, nb, current_stream_handle(), prime_group, flags)
     res = (ctypes.c_uint32 * MAX_PRIMES)()
     u = ctypes.c_uint64()
@@ -414,8 +425,7 @@ def count_plan(net: Network, plan: Plan, arith="auto", n_primes=0, workspace: Wo
     """Exact count (tn_count) of a built network under a plan."""
     lib = load()
     ws = workspace or default_workspace()
-    need = workspace_bytes(net, plan, arith, n_primes, prime_group, flags)
-    ptr, nb = ws.get(max(need, max_bytes))
+    ptr, nb = ws.get(max(_need(net, plan, arith, n_primes, prime_group, flags), max_bytes))
     o = _opts(arith, n_primes, ptr, nb, current_stream_handle(), prime_group, flags)
     cap = 80
     limbs = (ctypes.c_uint32 * cap)()
