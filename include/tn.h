@@ -14,9 +14,10 @@
  * run them on the GPU. Counts are exact (the paper's floating-point counts
  * lose precision from about 100 vertices, Sec. 3.2): 64-bit unsigned
  * arithmetic while the count is below 2^64 (at most 63 boolean variables;
- * plans of wide steps get there through the residues below); otherwise residues modulo the fewest small pairwise coprime moduli
- * (<= 255, one signed byte per residue) whose product exceeds twice the
- * largest possible count, or, beyond about 332 bits, modulo 16-bit primes;
+ * plans of wide steps get there through the residues below); otherwise
+ * residues modulo the fewest small pairwise coprime moduli (<= 255, one
+ * signed byte per residue) whose product exceeds twice the largest possible
+ * count, or, beyond about 332 bits, modulo 16-bit primes;
  * the residues are combined on the host by the Chinese remainder theorem at
  * a cost linear in the number of moduli.
  *
@@ -119,7 +120,10 @@ typedef struct {
 typedef enum { TN_ARITH_AUTO = 0, TN_ARITH_U64 = 1, TN_ARITH_RNS = 2 } tn_arith;
 
 typedef struct {
-    int32_t arith;            /* tn_arith; AUTO = U64 if n_vars <= 63 else RNS */
+    int32_t arith;            /* tn_arith; AUTO = U64 if n_vars <= 63 else RNS. U64 asked for is 64-bit
+                                 arithmetic; under AUTO a plan of at least 2^25 multiply-adds gets
+                                 to the same count through small moduli, as many planes at once as
+                                 the workspace holds */
     int32_t n_primes;         /* RNS: 0 = the fewest small moduli (see tn_moduli) or, if those do
                                  not hold 2^(n_vars + 1), the fewest primes of tn_primes that do;
                                  k > 0 = the first k primes of tn_primes */

@@ -852,8 +852,9 @@ static tn_status run_planes(const Network& net, const Plan& plan, const tn_contr
     return TN_OK;
 }
 
-bool residue_route(const Plan& plan, const Resolved& R, int flags, Resolved& rr) {
-    if (!R.u64 || !counts_by_residues(plan) || (flags & (TN_FLAG_GENERIC_ONLY | TN_FLAG_NO_MFMA))) return false;
+bool residue_route(const Plan& plan, const Resolved& R, const tn_contract_opts* o, Resolved& rr) {
+    if (!R.u64 || !counts_by_residues(plan)) return false;
+    if (o && (o->arith == TN_ARITH_U64 || (o->flags & (TN_FLAG_GENERIC_ONLY | TN_FLAG_NO_MFMA)))) return false;
     rr = Resolved{};
     rr.i8 = true;
     rr.k = small_moduli_needed(plan.count_bits);
@@ -875,7 +876,7 @@ static int64_t resident_planes(const Plan& plan, const Resolved& R, const tn_con
 tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,
                    std::vector<uint32_t>& residues, uint64_t* u64v, bool pinned) {
     Resolved rr;
-    if (!o || !residue_route(plan, R, o->flags, rr)) return run_planes(net, plan, o, R, residues, u64v, pinned);
+    if (!o || !residue_route(plan, R, o, rr)) return run_planes(net, plan, o, R, residues, u64v, pinned);
     // Groups of planes, as many of them resident as fit (a 64-bit plane's
     // workspace holds several: the option to keep few resident is about that
     // one plane). Every group after the first costs its launches again, 0.06 to
@@ -922,7 +923,7 @@ tn_status tn_workspace_bytes(const tn_network* net, const tn_plan* plan, const t
         plain_exec(plan->plan, plain);
         int64_t need = std::max(layout_of(plan->plan, *ex, R).bytes(G), layout_of(plan->plan, plain, R).bytes(G));
         Resolved rr;
-        if (residue_route(plan->plan, R, opts ? opts->flags : 0, rr)) {
+        if (residue_route(plan->plan, R, opts, rr)) {
             // one residue plane takes less than the 64-bit one; planes
             // asked to be resident together are the route's
             Exec rown;
