@@ -368,7 +368,7 @@ extern "C" tn_status tn_count_batch(const tn_formula* fs, int32_t n, tn_order_ki
         I.st = resolve(I.plan, opts, I.R);
         if (I.st != TN_OK) return;
         const Resolved asked = I.R;
-        if (Resolved rr; residue_route(I.plan, I.R, opts, rr)) I.R = rr;
+        if (Resolved rr; residue_route(I.net, I.plan, I.R, opts, rr)) I.R = rr;
         I.P = I.R.u64 ? 1 : I.R.k;
         I.es = I.R.es();
         I.res.assign(size_t(I.R.u64 ? 0 : I.R.k), 0);

@@ -637,13 +637,17 @@ void fill_init(const Network& net, const Plan& plan, const std::vector<int32_t>&
         put_init(net.t[size_t(ids[k])], plan.layout[size_t(ids[k])], el, mod, host + off[k] * elem_size(el), tmp);
 }
 
+// The largest initial entry a contraction meets: a plan may be run on another
+// network of its shape than the one it was made for (other weights).
+static uint64_t largest_entry(const Network& net, const Plan& plan) { return std::max(net.max_entry, plan.max_entry); }
+
 // Whether the initial entries must be reduced per residue plane: an int8
 // plane holds raw entries of at most 127 (any modulus), a u32 plane entries
 // below its prime.
-bool init_per_plane(const Plan& plan, const Resolved& R) {
+static bool init_per_plane(uint64_t max_entry, const Resolved& R) {
     if (R.u64) return false;
-    if (R.i8) return plan.max_entry > 127;
-    return plan.max_entry >= *std::min_element(R.primes.begin(), R.primes.end());
+    if (R.i8) return max_entry > 127;
+    return max_entry >= *std::min_element(R.primes.begin(), R.primes.end());
 }
 
 tn_status resolve(const Plan& plan, const tn_contract_opts* o, Resolved& r) {
@@ -695,10 +699,10 @@ struct Layout {
     }
 };
 
-Layout layout_of(const Plan& plan, const Exec& ex, const Resolved& R) {
+Layout layout_of(const Network& net, const Plan& plan, const Exec& ex, const Resolved& R) {
     Layout l{};
-    l.pp = init_per_plane(plan, R);
-    l.wide = plan.max_entry > 127;
+    l.pp = init_per_plane(largest_entry(net, plan), R);
+    l.wide = largest_entry(net, plan) > 127;
     l.blob = ex.progs.empty() ? 0 : blob_bytes(ex, l.wide);
     l.init = align256(ex.init_elems * int64_t(R.es()));
     l.arena = align256(ex.arena_elems * int64_t(R.es()));
@@ -743,7 +747,7 @@ static tn_status run_planes(const Network& net, const Plan& plan, const tn_contr
     const int64_t ws = int64_t(o->workspace_bytes);
     Exec own, plain;
     const Exec* ex = exec_of(plan, R, o->flags, own);
-    Layout lay = layout_of(plan, *ex, R);
+    Layout lay = layout_of(net, plan, *ex, R);
     const int64_t want = std::min<int64_t>({int64_t(R.k), int64_t(kMaxGroup),
                                             o->prime_group > 0 ? int64_t(o->prime_group) : int64_t(kMaxGroup)});
     int64_t fit = std::min(lay.planes(ws), want);
@@ -751,7 +755,7 @@ static tn_status run_planes(const Network& net, const Plan& plan, const tn_contr
         // the fused layout keeps every program's result from the start: a
         // tight workspace may hold more planes step by step
         plain_exec(plan, plain);
-        const Layout pl = layout_of(plan, plain, R);
+        const Layout pl = layout_of(net, plan, plain, R);
         const int64_t pf = std::min(pl.planes(ws), want);
         if (pf > fit) {
             ex = &plain;
@@ -852,31 +856,33 @@ static tn_status run_planes(const Network& net, const Plan& plan, const tn_contr
     return TN_OK;
 }
 
-bool residue_route(const Plan& plan, const Resolved& R, const tn_contract_opts* o, Resolved& rr) {
-    if (!R.u64 || !counts_by_residues(plan)) return false;
+bool residue_route(const Network& net, const Plan& plan, const Resolved& R, const tn_contract_opts* o, Resolved& rr) {
+    // (the plan may be another network's of the same shape)
+    const int32_t bits = std::max(net.count_bits, plan.count_bits);
+    if (!R.u64 || !counts_by_residues(plan) || bits > 63) return false;
     if (o && (o->arith == TN_ARITH_U64 || (o->flags & (TN_FLAG_GENERIC_ONLY | TN_FLAG_NO_MFMA)))) return false;
     rr = Resolved{};
     rr.i8 = true;
-    rr.k = small_moduli_needed(plan.count_bits);
+    rr.k = small_moduli_needed(bits);
     const auto& M = small_moduli();
     rr.primes.assign(M.begin(), M.begin() + rr.k);
     return true;
 }
 
 // Planes of R that the workspace holds at a time, by either layout.
-static int64_t resident_planes(const Plan& plan, const Resolved& R, const tn_contract_opts* o) {
+static int64_t resident_planes(const Network& net, const Plan& plan, const Resolved& R, const tn_contract_opts* o) {
     Exec own, plain;
     plain_exec(plan, plain);
     const int64_t ws = int64_t(o->workspace_bytes);
-    return std::min<int64_t>(std::max(layout_of(plan, *exec_of(plan, R, o->flags, own), R).planes(ws),
-                                      layout_of(plan, plain, R).planes(ws)),
+    return std::min<int64_t>(std::max(layout_of(net, plan, *exec_of(plan, R, o->flags, own), R).planes(ws),
+                                      layout_of(net, plan, plain, R).planes(ws)),
                              std::min(R.k, kMaxGroup));
 }
 
 tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,
                    std::vector<uint32_t>& residues, uint64_t* u64v, bool pinned) {
     Resolved rr;
-    if (!o || !residue_route(plan, R, o, rr)) return run_planes(net, plan, o, R, residues, u64v, pinned);
+    if (!o || !residue_route(net, plan, R, o, rr)) return run_planes(net, plan, o, R, residues, u64v, pinned);
     // Groups of planes, as many of them resident as fit (a 64-bit plane's
     // workspace holds several: the option to keep few resident is about that
     // one plane). Every group after the first costs its launches again, 0.06 to
@@ -884,7 +890,7 @@ tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts*
     // multiply-adds, 64-bit 0.127 ms against 0.088 / 0.144 / 0.203 in 1 / 2 / 3
     // groups; 3e8, 0.372 against 0.109 / 0.187 / 0.265, 0.499 in 6; 1.2e9, 1.11 against
     // 0.685 in 7.
-    const int64_t fit = resident_planes(plan, rr, o);
+    const int64_t fit = resident_planes(net, plan, rr, o);
     if (fit >= 1) {
         const int64_t groups = (rr.k + fit - 1) / fit;
         if (groups > 1 && plan.stats.macs < kResidueMacs + double(groups - 1) * kResidueGroupMacs) {
@@ -921,15 +927,16 @@ tn_status tn_workspace_bytes(const tn_network* net, const tn_plan* plan, const t
         Exec own, plain;
         const Exec* ex = exec_of(plan->plan, R, opts ? opts->flags : 0, own);
         plain_exec(plan->plan, plain);
-        int64_t need = std::max(layout_of(plan->plan, *ex, R).bytes(G), layout_of(plan->plan, plain, R).bytes(G));
+        int64_t need = std::max(layout_of(net->net, plan->plan, *ex, R).bytes(G),
+                                layout_of(net->net, plan->plan, plain, R).bytes(G));
         Resolved rr;
-        if (residue_route(plan->plan, R, opts, rr)) {
+        if (residue_route(net->net, plan->plan, R, opts, rr)) {
             // one residue plane takes less than the 64-bit one; planes
             // asked to be resident together are the route's
             Exec rown;
             const Exec* rex = exec_of(plan->plan, rr, 0, rown);
             const int RG = opts && opts->prime_group > 0 ? std::min({opts->prime_group, rr.k, kMaxGroup}) : 1;
-            need = std::max(need, layout_of(plan->plan, *rex, rr).bytes(RG));
+            need = std::max(need, layout_of(net->net, plan->plan, *rex, rr).bytes(RG));
         }
         *bytes = size_t(need);
     } catch (const std::bad_alloc&) {

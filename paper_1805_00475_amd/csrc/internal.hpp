@@ -180,7 +180,7 @@ inline bool counts_by_residues(const Plan& plan) {
 }
 // The moduli of that route for a contraction resolved to 64-bit counts;
 // false: it stays as it is (also where 64-bit arithmetic was asked for).
-bool residue_route(const Plan& plan, const Resolved& R, const tn_contract_opts* o, Resolved& rr);
+bool residue_route(const Network& net, const Plan& plan, const Resolved& R, const tn_contract_opts* o, Resolved& rr);
 // Runs the plan; fills residues (RNS) or *u64v (U64).
 // pinned: the call may use pinned host staging memory (which it allocates)
 tn_status run_plan(const Network& net, const Plan& plan, const tn_contract_opts* o, const Resolved& R,

@@ -78,6 +78,5 @@ hipError_t launch_stream_step(const StepArgs& a, int el, int G, int nb, hipStrea
 // (reduced modulo *mod when given).
 void fill_init(const Network& net, const Plan& plan, const std::vector<int32_t>& ids,
                const std::vector<int64_t>& off, int el, uint8_t* host, const uint32_t* mod = nullptr);
-bool init_per_plane(const Plan& plan, const Resolved& R);
 
 }  // namespace tn
