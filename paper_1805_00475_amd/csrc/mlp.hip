@@ -102,8 +102,9 @@ __device__ __forceinline__ void mul_tile(const float (&tile)[16 * RT][kPad], con
         }
 }
 
-// All three layers of 16 RT rows per tile.
-template <int RT>
+// The layers of LAYERS (bit l - 1: layer l) for 16 RT rows per tile: all three, or
+// one, which takes the other layer's rows from memory.
+template <int RT, int LAYERS>
 __global__ __launch_bounds__(kThreads) void k_forward(const float* P, const float* X, int64_t n, float* H1, float* H2,
                                                       float* y) {
     __shared__ __align__(16) float t1[16 * RT][kPad];
@@ -117,65 +118,80 @@ __global__ __launch_bounds__(kThreads) void k_forward(const float* P, const floa
     const float b1 = P[kOffB1 + j];
     v4f wf[2][8];
     float b2[2];
+    if constexpr (LAYERS & 2) {
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-        const int col = 32 * w + 16 * cb + fr;
+        for (int cb = 0; cb < 2; ++cb) {
+            const int col = 32 * w + 16 * cb + fr;
 #pragma unroll
-        for (int kb = 0; kb < 8; ++kb)
-            wf[cb][kb] = transpose4(*reinterpret_cast<const v4u*>(P + kOffW2 + col * H + 16 * kb + 4 * q));
-        b2[cb] = P[kOffB2 + col];
+            for (int kb = 0; kb < 8; ++kb)
+                wf[cb][kb] = transpose4(*reinterpret_cast<const v4u*>(P + kOffW2 + col * H + 16 * kb + 4 * q));
+            b2[cb] = P[kOffB2 + col];
+        }
     }
     const float w3[2] = {P[kOffW3 + lane], P[kOffW3 + lane + 64]}, b3 = P[kOffB3];
     const int64_t tiles = (n + 16 * RT - 1) / (16 * RT);
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const int64_t base = tile * (16 * RT);
         __syncthreads();
-        for (int e = t; e < 16 * RT * F; e += kThreads) sx[e / F][e % F] = base + e / F < n ? X[base * F + e] : 0.0f;
-        __syncthreads();
+        if constexpr (LAYERS & 1) {
+            for (int e = t; e < 16 * RT * F; e += kThreads)
+                sx[e / F][e % F] = base + e / F < n ? X[base * F + e] : 0.0f;
+            __syncthreads();
+        }
 #pragma unroll 4
         for (int r = t >> 7; r < 16 * RT; r += 2) {
             const int64_t i = base + r;
             float h = 0.0f;
             if (i < n) {
-                float a = b1;
+                if constexpr (LAYERS & 1) {
+                    float a = b1;
 #pragma unroll
-                for (int k = 0; k < F; ++k) a += w1[k] * sx[r][k];
-                h = a > 0.0f ? a : 0.0f;
-                H1[i * H + j] = h;
-            }
-            t1[r][place(j)] = h;
-        }
-        __syncthreads();
-        v4f acc[RT][2];
-#pragma unroll
-        for (int rb = 0; rb < RT; ++rb)
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = v4f{b2[cb], b2[cb], b2[cb], b2[cb]};
-        mul_tile<RT>(t1, wf, lane, acc);
-#pragma unroll
-        for (int rb = 0; rb < RT; ++rb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = 16 * rb + 4 * q + v;
-                const int64_t i = base + r;
-#pragma unroll
-                for (int cb = 0; cb < 2; ++cb) {
-                    const float a = acc[rb][cb][v];
-                    const float h = a > 0.0f ? a : 0.0f;
-                    if (i < n) H2[i * H + 32 * w + 16 * cb + fr] = h;
-                    t2[r][32 * w + 16 * cb + fr] = h;
+                    for (int k = 0; k < F; ++k) a += w1[k] * sx[r][k];
+                    h = a > 0.0f ? a : 0.0f;
+                    H1[i * H + j] = h;
+                } else if constexpr (LAYERS & 2) {
+                    h = H1[i * H + j];
+                } else {
+                    t2[r][j] = H2[i * H + j];
                 }
             }
-        __syncthreads();
-        // layer 3: a wavefront per row, 4 RT of them side by side
-        float s3 = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 4 * RT; ++r) {
-            const float a = wave_sum(w3[0] * t2[4 * r + w][lane] + w3[1] * t2[4 * r + w][lane + 64]);
-            s3 = lane == r ? a : s3;
+            if constexpr (LAYERS & 2) t1[r][place(j)] = h;
         }
-        const int64_t i = base + 4 * lane + w;
-        if (lane < 4 * RT && i < n) y[i] = s3 + b3;
+        __syncthreads();
+        if constexpr (LAYERS & 2) {
+            v4f acc[RT][2];
+#pragma unroll
+            for (int rb = 0; rb < RT; ++rb)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = v4f{b2[cb], b2[cb], b2[cb], b2[cb]};
+            mul_tile<RT>(t1, wf, lane, acc);
+#pragma unroll
+            for (int rb = 0; rb < RT; ++rb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = 16 * rb + 4 * q + v;
+                    const int64_t i = base + r;
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) {
+                        const float a = acc[rb][cb][v];
+                        const float h = a > 0.0f ? a : 0.0f;
+                        if (i < n) H2[i * H + 32 * w + 16 * cb + fr] = h;
+                        t2[r][32 * w + 16 * cb + fr] = h;
+                    }
+                }
+            __syncthreads();
+        }
+        if constexpr (LAYERS & 4) {
+            // a wavefront per row, 4 RT of them side by side
+            float s3 = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 4 * RT; ++r) {
+                const float a = wave_sum(w3[0] * t2[4 * r + w][lane] + w3[1] * t2[4 * r + w][lane + 64]);
+                s3 = lane == r ? a : s3;
+            }
+            const int64_t i = base + 4 * lane + w;
+            if (lane < 4 * RT && i < n) y[i] = s3 + b3;
+        }
     }
 }
 
@@ -460,11 +476,20 @@ tn_status tn_mlp_forward(const float* P, const float* X, int64_t n, float* H1, f
     if (!P || n < 0 || (n > 0 && (!X || !H1 || !H2 || !y))) return TN_EINVAL;
     if (n == 0) return TN_OK;
     hipStream_t s = static_cast<hipStream_t>(stream_);
-    // 32-row tiles once they fill the GPU, 16-row tiles below
-    if (n >= kManyRows)
-        hipLaunchKernelGGL(k_forward<2>, dim3(blocks_for(n, 32, 1024)), dim3(kThreads), 0, s, P, X, n, H1, H2, y);
-    else
-        hipLaunchKernelGGL(k_forward<1>, dim3(blocks_for(n, 16, 1024)), dim3(kThreads), 0, s, P, X, n, H1, H2, y);
+    const auto meet = [](const float* p, int64_t np, const float* q, int64_t nq) { return p < q + nq && q < p + np; };
+    const dim3 g1(blocks_for(n, 16, 1024)), g2(blocks_for(n, 32, 1024)), block(kThreads);
+    if (meet(H2, n * H, X, n * F) || meet(y, n, X, n * F) || meet(y, n, H1, n * H)) {
+        // an output lies where an earlier layer's rows are still to be read:
+        // layer by layer
+        hipLaunchKernelGGL((k_forward<1, 1>), g1, block, 0, s, P, X, n, H1, H2, y);
+        hipLaunchKernelGGL((k_forward<1, 2>), g1, block, 0, s, P, X, n, H1, H2, y);
+        hipLaunchKernelGGL((k_forward<1, 4>), g1, block, 0, s, P, X, n, H1, H2, y);
+    } else if (n >= kManyRows) {
+        // 32-row tiles once they fill the GPU, 16-row tiles below
+        hipLaunchKernelGGL((k_forward<2, 7>), g2, block, 0, s, P, X, n, H1, H2, y);
+    } else {
+        hipLaunchKernelGGL((k_forward<1, 7>), g1, block, 0, s, P, X, n, H1, H2, y);
+    }
     return hipGetLastError() == hipSuccess ? TN_OK : TN_EHIP;
 }
 
