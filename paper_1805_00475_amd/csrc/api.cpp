@@ -11,6 +11,7 @@
 #include <new>
 #include <thread>
 
+#include "fuse.hpp"
 #include "graph.hpp"
 #include "internal.hpp"
 
@@ -359,6 +360,7 @@ tn_status make_order(const Network& N, int32_t kind, uint64_t seed, const tn_mod
                 out.cost_us = -1;
                 out.cost_us = plan_cost(out);
                 out.stats.log2_cost = out.cost_us > 0 ? std::log2(out.cost_us) : 0.0;
+                keep_exec(out);
             }
         }
         if (kind == TN_ORDER_LEARNED && have) out.stats.fallback = out.stats.chosen != TN_ORDER_LEARNED;

@@ -70,9 +70,12 @@ void fill_blob(const Network& net, const Plan& plan, const Exec& ex, bool wide, 
 
 // The fused execution of a plan for an element size of es bytes.
 void build_exec(const Plan& plan, int es, Exec& ex);
+// Keeps the plan's execution for its default arithmetic with it; once the plan
+// has its steps, and again when its count bound changes.
+void keep_exec(Plan& plan);
 // The plan step by step.
 void plain_exec(const Plan& plan, Exec& ex);
-// Kept with the plan for its default arithmetic (make_plan); nullptr when the
+// Kept with the plan for its default arithmetic (keep_exec); nullptr when the
 // plan holds none for this element size.
 const Exec* plan_exec(const Plan& plan, int es);
 

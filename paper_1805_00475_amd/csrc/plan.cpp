@@ -185,6 +185,16 @@ tn_status sketch_plan(const Network& net, std::vector<std::pair<int32_t, int32_t
     return TN_OK;
 }
 
+void keep_exec(Plan& plan) {
+    const int mode = default_residue_mode(plan.count_bits);
+    const int32_t es = mode == RM_WIDE ? 4 : mode == RM_SMALL || counts_by_residues(plan) ? 1 : 8;
+    if (plan.exec && plan.exec_es == es) return;
+    auto ex = std::make_shared<Exec>();
+    build_exec(plan, es, *ex);
+    plan.exec = std::move(ex);
+    plan.exec_es = es;
+}
+
 tn_status make_plan(const Network& net, std::vector<std::pair<int32_t, int32_t>> merges, int32_t chosen,
                     Plan& plan) {
     try {
@@ -315,11 +325,7 @@ tn_status make_plan(const Network& net, std::vector<std::pair<int32_t, int32_t>>
         plan.stats.log2_cost = c > 0 ? std::log2(c) : 0.0;
         plan.stats.chosen = chosen;
         plan.stats.fallback = 0;
-        const int mode = default_residue_mode(plan.count_bits);
-        plan.exec_es = mode == RM_WIDE ? 4 : mode == RM_SMALL || counts_by_residues(plan) ? 1 : 8;
-        auto ex = std::make_shared<Exec>();
-        build_exec(plan, plan.exec_es, *ex);
-        plan.exec = std::move(ex);
+        keep_exec(plan);
     } catch (const std::bad_alloc&) {
         return TN_ENOMEM;
     }
