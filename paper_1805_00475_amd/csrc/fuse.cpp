@@ -224,6 +224,7 @@ void build_exec(const Plan& plan, int es, Exec& ex) {
         pg.lds_elems = uint32_t(lds.high);
         ex.lds_bytes = std::max(ex.lds_bytes, lds_of(pg, es));
         ex.progs.push_back(pg);
+        ex.prog_out.push_back(plan.steps[size_t(r)].out);
         root_step.push_back(r);
     }
     ex.pinit_first.push_back(int32_t(ex.pinit.size()));

@@ -47,6 +47,7 @@ struct Exec {
     std::vector<int32_t> pinit;         // initial tensors of the programs, in program order
     std::vector<int32_t> pinit_first;   // first of them per program (one more at the end)
     std::vector<uint32_t> pinit_off;    // their LDS entries
+    std::vector<int32_t> prog_out;      // the tensor each program ends in
     uint32_t prog_end = 0;              // bytes of headers and programs
     uint32_t n_entries = 0;             // initial entries of all programs
     uint32_t lds_bytes = 0;             // LDS of the largest program
@@ -75,6 +76,11 @@ void build_exec(const Plan& plan, int es, Exec& ex);
 void keep_exec(Plan& plan);
 // The plan step by step.
 void plain_exec(const Plan& plan, Exec& ex);
+// Checks an execution's layout against the liveness of its tensors: no tensor
+// may overlap another one that is alive at the same time. Programs' results are
+// written first and stay until they are read, where they are read; a program's
+// LDS accesses stay within what it asks for.
+tn_status verify_exec(const Plan& plan, const Exec& ex, int es);
 // Kept with the plan for its default arithmetic (keep_exec); nullptr when the
 // plan holds none for this element size.
 const Exec* plan_exec(const Plan& plan, int es);

@@ -336,15 +336,38 @@ tn_status make_plan(const Network& net, std::vector<std::pair<int32_t, int32_t>>
 
 namespace tn {
 
-// Checks an execution's arena layout against the liveness of its tensors: no
-// tensor may overlap another one that is alive at the same time. Programs'
-// results are written first (step -1) and stay until they are read.
-static tn_status verify_exec(const Plan& plan, const Exec& ex) {
+tn_status verify_exec(const Plan& plan, const Exec& ex, int es) {
     const int32_t n_ids = plan.n_init + int32_t(plan.steps.size());
     const int32_t n = int32_t(ex.steps.size());
-    std::vector<int32_t> born(size_t(n_ids), n + 1), died(size_t(n_ids), n);
+    std::vector<int32_t> born(size_t(n_ids), n + 1), died(size_t(n_ids), -2);
     std::vector<int64_t> off(size_t(n_ids), -1), size(size_t(n_ids), 0);
     std::vector<int32_t> ids;
+    // the programs' results, written before step 0, and their LDS accesses
+    if (ex.prog_out.size() != ex.progs.size()) return TN_EINVAL;
+    size_t step = 0;
+    for (size_t i = 0; i < ex.progs.size(); ++i) {
+        const FuseProg& pg = ex.progs[i];
+        const int32_t id = ex.prog_out[i];
+        if (id < plan.n_init || id >= n_ids || born[size_t(id)] <= n) return TN_EINVAL;
+        if ((pg.final != 0) != (id == plan.root)) return TN_EINVAL;
+        if (lds_of(pg, es) > kMaxProgramLds || pg.n_init > pg.lds_elems) return TN_EINVAL;
+        for (uint32_t k = 0; k < pg.n_steps; ++k, ++step) {
+            const FuseStep& st = ex.psteps[step];
+            const int s = st.sr & 0xff, rC = (st.sr >> 8) & 0x7f, fA = __builtin_popcount(st.maskA);
+            const auto inside = [&](uint32_t o, int rank) { return uint64_t(o) + (uint64_t(1) << rank) <= pg.lds_elems; };
+            if (!inside(st.offA, fA + s) || !inside(st.offB, rC - fA + s)) return TN_EINVAL;
+            if (!(st.sr & kFuseRoot) && !inside(st.offC, rC)) return TN_EINVAL;
+        }
+        born[size_t(id)] = -1;
+        if (pg.final) {
+            died[size_t(id)] = n;
+            continue;
+        }
+        if (pg.root_rank != plan.rank[size_t(id)]) return TN_EINVAL;
+        off[size_t(id)] = pg.root_off;
+        size[size_t(id)] = int64_t(1) << pg.root_rank;
+        ids.push_back(id);
+    }
     for (int32_t k = 0; k < n; ++k) {
         const Step& st = ex.steps[size_t(k)];
         for (int side = 0; side < 2; ++side) {
@@ -352,13 +375,7 @@ static tn_status verify_exec(const Plan& plan, const Exec& ex) {
             const bool init = side ? st.initB : st.initA;
             const int64_t o = side ? st.offB : st.offA;
             if (init) continue;
-            if (born[size_t(id)] > n) {  // a program's result
-                born[size_t(id)] = -1;
-                off[size_t(id)] = o;
-                size[size_t(id)] = int64_t(1) << plan.rank[size_t(id)];
-                ids.push_back(id);
-            }
-            if (off[size_t(id)] != o) return TN_EINVAL;
+            if (born[size_t(id)] >= k || off[size_t(id)] != o) return TN_EINVAL;
             died[size_t(id)] = k;
         }
         born[size_t(st.out)] = k;
@@ -366,9 +383,10 @@ static tn_status verify_exec(const Plan& plan, const Exec& ex) {
         size[size_t(st.out)] = int64_t(1) << st.rC;
         ids.push_back(st.out);
     }
+    if (n > 0 && plan.root >= plan.n_init) died[size_t(plan.root)] = n;
     for (size_t i = 0; i < ids.size(); ++i) {
         const size_t x = size_t(ids[i]);
-        if (off[x] < 0 || off[x] + size[x] > ex.arena_elems) return TN_EINVAL;
+        if (off[x] < 0 || off[x] + size[x] > ex.arena_elems || died[x] < -1) return TN_EINVAL;
         for (size_t j = i + 1; j < ids.size(); ++j) {
             const size_t y = size_t(ids[j]);
             // inputs stay live through the step that reads them
@@ -384,11 +402,11 @@ static tn_status verify_exec(const Plan& plan, const Exec& ex) {
 tn_status verify_plan(const Plan& plan) {
     Exec ex;
     plain_exec(plan, ex);
-    tn_status st = verify_exec(plan, ex);
+    tn_status st = verify_exec(plan, ex, 8);
     for (int es : {1, 4, 8}) {
         if (st != TN_OK) return st;
         build_exec(plan, es, ex);
-        st = verify_exec(plan, ex);
+        st = verify_exec(plan, ex, es);
     }
     return st;
 }
