@@ -473,7 +473,11 @@ tn_status tn_plan_steps(const tn_plan* plan, int32_t* pairs, int32_t cap, int32_
 
 tn_status tn_plan_verify(const tn_plan* plan) {
     if (!plan) return TN_EINVAL;
-    return verify_plan(plan->plan);
+    try {
+        return verify_plan(plan->plan);
+    } catch (const std::bad_alloc&) {
+        return TN_ENOMEM;
+    }
 }
 
 tn_status tn_primes(int32_t k, uint32_t* out) {

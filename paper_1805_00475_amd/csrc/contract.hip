@@ -919,11 +919,11 @@ extern "C" {
 tn_status tn_workspace_bytes(const tn_network* net, const tn_plan* plan, const tn_contract_opts* opts,
                              size_t* bytes) {
     if (!net || !plan || !bytes) return TN_EINVAL;
-    Resolved R;
-    tn_status st = resolve(plan->plan, opts, R);
-    if (st != TN_OK) return st;
-    const int G = (opts && opts->prime_group > 0) ? std::min<int>(opts->prime_group, std::min(R.k, kMaxGroup)) : 1;
     try {
+        Resolved R;
+        const tn_status st = resolve(plan->plan, opts, R);
+        if (st != TN_OK) return st;
+        const int G = (opts && opts->prime_group > 0) ? std::min<int>(opts->prime_group, std::min(R.k, kMaxGroup)) : 1;
         Exec own, plain;
         const Exec* ex = exec_of(plan->plan, R, opts ? opts->flags : 0, own);
         plain_exec(plan->plan, plain);
