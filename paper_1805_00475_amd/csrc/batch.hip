@@ -214,7 +214,9 @@ tn_status run_sub(std::vector<Inst>& ins, const SubBatch& sb, const tn_contract_
 
     Profiler& prof = profiler();
     // the side streams are drained by their owner before anything above goes
-    // away; on a failure the caller's stream is too
+    // away, and the caller's by its guard where a failure or an exception ends
+    // the call first
+    DrainGuard guard(stream);
     SideStreams side(std::min<int>(chains, int(list.size())) - 1);
     auto fail = [&]() {
         for (size_t k = 0; k < side.size(); ++k) (void)hipStreamSynchronize(side[k].stream);
@@ -282,6 +284,7 @@ tn_status run_sub(std::vector<Inst>& ins, const SubBatch& sb, const tn_contract_
         err = hipMemcpyAsync(out.data(), d_res, out.size() * 8, hipMemcpyDeviceToHost, stream);
     if (err != hipSuccess) return fail();
     if (hipStreamSynchronize(stream) != hipSuccess) return fail();
+    guard.drained();
     prof.collect();
     for (int32_t i : sb.ids) {
         Inst& I = ins[size_t(i)];

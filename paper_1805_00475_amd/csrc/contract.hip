@@ -24,6 +24,7 @@
 #include "profile.hpp"
 #include "launch.hpp"
 #include "pinned.hpp"
+#include "streams.hpp"
 #include "tune.hpp"
 
 namespace tn {
@@ -790,7 +791,8 @@ static tn_status run_planes(const Network& net, const Plan& plan, const tn_contr
     for (int q = 0; pp && q < R.k; ++q)
         fill_init(net, plan, ex->init_ids, ex->init_off, el, pp_img + int64_t(q) * init_bytes, &R.primes[size_t(q)]);
     Profiler& prof = profiler();
-    // on any failure, drain the stream before the host staging goes away
+    // on any failure the stream is drained before the host staging goes away
+    // (by the guards where an exception ends the call)
     auto fail = [&]() {
         (void)hipStreamSynchronize(stream);
         prof.collect();
@@ -804,6 +806,7 @@ static tn_status run_planes(const Network& net, const Plan& plan, const tn_contr
     // where each group's are copied
     std::vector<uint64_t> out(size_t(R.k), 0);
     hipError_t err = hipSuccess;
+    DrainGuard guard(stream);
     if (head > 0)
         err = staged ? launch_upload(img, blob_base, head / 16, stream)
                      : hipMemcpyAsync(blob_base, img, size_t(head), hipMemcpyHostToDevice, stream);
@@ -839,7 +842,8 @@ static tn_status run_planes(const Network& net, const Plan& plan, const tn_contr
         if (err != hipSuccess) return fail();
     }
     err = hipStreamSynchronize(stream);
-    if (err != hipSuccess) return TN_EHIP;
+    if (err != hipSuccess) return fail();
+    guard.drained();
     prof.collect();
     if (pin.p) std::copy(pin.results(), pin.results() + R.k, out.begin());
     if (R.u64) {

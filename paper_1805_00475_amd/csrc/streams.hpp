@@ -65,6 +65,24 @@ class StreamPool {
     std::vector<std::pair<int, SideStream>> idle_;
 };
 
+// Waits for a stream where a scope ends before drained(): by an error's return
+// or an exception. Declared after the host buffers that the stream's copies
+// use, so that they go away behind it.
+class DrainGuard {
+  public:
+    explicit DrainGuard(hipStream_t s) : stream_(s) {}
+    ~DrainGuard() {
+        if (!drained_) (void)hipStreamSynchronize(stream_);
+    }
+    DrainGuard(const DrainGuard&) = delete;
+    DrainGuard& operator=(const DrainGuard&) = delete;
+    void drained() { drained_ = true; }
+
+  private:
+    hipStream_t stream_;
+    bool drained_ = false;
+};
+
 // Up to n side streams for the length of a call; they are drained before
 // they go back.
 class SideStreams {
