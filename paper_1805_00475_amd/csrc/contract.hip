@@ -806,6 +806,7 @@ static tn_status run_planes(const Network& net, const Plan& plan, const tn_contr
     // where each group's are copied
     std::vector<uint64_t> out(size_t(R.k), 0);
     hipError_t err = hipSuccess;
+    pin.in_use(stream);
     DrainGuard guard(stream);
     if (head > 0)
         err = staged ? launch_upload(img, blob_base, head / 16, stream)
@@ -844,6 +845,7 @@ static tn_status run_planes(const Network& net, const Plan& plan, const tn_contr
     err = hipStreamSynchronize(stream);
     if (err != hipSuccess) return fail();
     guard.drained();
+    pin.drained();
     prof.collect();
     if (pin.p) std::copy(pin.results(), pin.results() + R.k, out.begin());
     if (R.u64) {

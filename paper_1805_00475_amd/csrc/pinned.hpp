@@ -57,16 +57,29 @@ class PinnedPool {
     std::vector<uint8_t*> free_;
 };
 
-// A block for the length of a call.
+// A block for the length of a call. Between in_use and drained a stream may
+// read and write it: a call that ends in between waits for the stream, and
+// where even that fails the block stays out of the pool, since the next call's
+// results would lie where the stream may still write.
 struct PinnedBlock {
     uint8_t* p = nullptr;
     explicit PinnedBlock(bool want) : p(want ? PinnedPool::get().take() : nullptr) {}
     ~PinnedBlock() {
-        if (p) PinnedPool::get().give(p);
+        if (!p || (busy_ && hipStreamSynchronize(stream_) != hipSuccess)) return;
+        PinnedPool::get().give(p);
     }
+    void in_use(hipStream_t s) {
+        stream_ = s;
+        busy_ = true;
+    }
+    void drained() { busy_ = false; }
     PinnedBlock(const PinnedBlock&) = delete;
     PinnedBlock& operator=(const PinnedBlock&) = delete;
     uint64_t* results() const { return reinterpret_cast<uint64_t*>(p + PinnedPool::kUpload); }
+
+  private:
+    hipStream_t stream_ = nullptr;
+    bool busy_ = false;
 };
 
 }  // namespace tn

@@ -1,9 +1,10 @@
 // Host buffers of a call outlive the stream that uses them, whichever way the
-// call ends (streams.hpp over a stub of the runtime).
+// call ends (streams.hpp, pinned.hpp over a stub of the runtime).
 #include <cstdio>
 #include <new>
 #include <vector>
 
+#include "pinned.hpp"
 #include "streams.hpp"
 
 using namespace tn;
@@ -48,6 +49,35 @@ int main() {
         check(side.size() == 2, "side streams");
     }
     check(stub_syncs == 3, "side streams and the caller's are drained");
+
+    // pinned blocks: the pool holds what was given back
+    uint8_t* first;
+    {
+        PinnedBlock b(true);
+        first = b.p;
+        b.in_use(&s);
+        b.drained();
+    }
+    stub_syncs = 0;
+    {
+        PinnedBlock b(true);
+        check(b.p == first, "a drained block is used again");
+        b.in_use(&s);
+    }
+    check(stub_syncs == 1, "a block in use is drained before it is given back");
+    {
+        PinnedBlock b(true);
+        check(b.p == first, "and then used again");
+        b.in_use(&s);
+        stub_sync_result = hipErrorUnknown;
+    }
+    stub_sync_result = hipSuccess;
+    {
+        PinnedBlock b(true);
+        check(b.p && b.p != first, "a block that could not be drained is not used again");
+    }
+    PinnedBlock none(false);
+    check(!none.p, "no block unless wanted");
     if (!bad) std::printf("ok\n");
     return bad;
 }
