@@ -53,9 +53,17 @@ def test_sums_ascend(n):
     dev = [torch.from_numpy(a).cuda() for a in (p, x, lab, g)]
     tn.mlp_forward(dev[0], dev[1], h1, h2, y)
     tn.mlp_backward(dev[0], dev[1], h1, h2, y, dev[2], dev[3], grad, dz2, dz1, dy, loss)
-    h1, h2, dz1, dz2, dy = (t.cpu().numpy() for t in (h1, h2, dz1, dz2, dy))
+    h1, h2, dz1, dz2, dy, y = (t.cpu().numpy() for t in (h1, h2, dz1, dz2, dy, y))
     w1, b1, w2, b2, w3, _ = (np.asarray(a, dtype=np.float32) for a in mlp.unpack(p))
     assert np.array_equal(h1, np.maximum(_chain(x, w1.T, b1), 0))
     assert np.array_equal(h2, np.maximum(_chain(h1, w2.T, b2), 0))
     assert np.array_equal(dz2, np.where(h2 > 0, dy[:, None] * w3, np.float32(0)))
     assert np.array_equal(dz1, np.where(h1 > 0, _chain(dz2, w2, np.float32(0)), np.float32(0)))
+    # dy from the scores in double: exponentials to 2 ulp of arguments rounded
+    # once, sums of a group's rows, two quotients, a difference of numbers <= 1
+    y = y.astype(np.float64)
+    for a, b in zip(g[:-1], g[1:]):
+        e = np.exp(y[a:b] - y[a:b].max())
+        want = (e / e.sum() - e * lab[a:b] / (e * lab[a:b]).sum()) / groups
+        bound = 2 * (b - a + np.ptp(y[a:b]) + 8) * 2.0 ** -24 / groups
+        assert np.abs(dy[a:b] - want).max() <= bound
