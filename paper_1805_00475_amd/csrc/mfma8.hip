@@ -687,13 +687,12 @@ __global__ __launch_bounds__(256) void k_mfma8_reduce(StepArgs a, const int8_t* 
 // rows consecutive in memory, so a wave's fragment load covers 16 whole rows)
 // -- 8 bytes at K offset 8 q, zero where 8 q >= K -- and one
 // v_mfma_i32_16x16x32_i8 per 16x16 block gives the exact sums (at most
-// 32 127^2 < 2^21). Such steps are bound by writing C. A wave takes U tiles
-// per round: their fragments are requested together (each set as soon as its
-// tile's products are issued) and one wait per round covers them. (Loads and
-// stores share one completion counter, so that wait also covers the stores
-// before it; measured on the largest 1-in-3 configuration, U = 2 and 4 are no
-// faster than U = 1.)
-template <class G, int S, int U = 1>
+// 32 127^2 < 2^21). Such steps are bound by writing C. The next tile's
+// fragments are requested as soon as a tile's products are issued. (Loads and
+// stores share one completion counter, so the wait for them also covers the
+// stores before; two or four tiles per wait were no faster on the largest
+// 1-in-3 configuration.)
+template <class G, int S>
 __global__ __launch_bounds__(G::THREADS) void k_mfma8_short(StepArgs a, Mfma8Extra ex) {
     constexpr int RA = G::RA, CB = G::CB, K = 1 << S;
     __shared__ __align__(1024) uint8_t stage[G::NW * Piece<RA, CB>::BYTES];
@@ -725,44 +724,36 @@ __global__ __launch_bounds__(G::THREADS) void k_mfma8_short(StepArgs a, Mfma8Ext
             return frag_t(*reinterpret_cast<const uint8_t*>(p));
         }
     };
-    frag_t fa[U][RA], fb[U][CB];
-    auto fetch = [&](uint32_t tile, int u) {
+    frag_t fa[RA], fb[CB];
+    auto fetch = [&](uint32_t tile) {
         uint32_t ta, tb;
         tile_coords_lg(tile, lgA, lgB, ta, tb);
         const int8_t* pA = A + uint64_t(ta) * G::WM * K + offA;
         const int8_t* pB = B + uint64_t(tb) * G::WN * K + offB;
 #pragma unroll
-        for (int rb = 0; rb < RA; ++rb) fa[u][rb] = load(pA + 16 * K * rb);
+        for (int rb = 0; rb < RA; ++rb) fa[rb] = load(pA + 16 * K * rb);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) fb[u][cb] = load(pB + 16 * K * cb);
+        for (int cb = 0; cb < CB; ++cb) fb[cb] = load(pB + 16 * K * cb);
     };
-    const uint32_t stride = gridDim.x;
     uint32_t tile = blockIdx.x;
     if (tile >= T) return;
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-        if (tile + u * stride < T) fetch(tile + u * stride, u);
+    fetch(tile);
     for (;;) {
+        v4i acc[RA][CB];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t t = tile + u * stride;
-            if (t >= T) break;
-            v4i acc[RA][CB];
+        for (int rb = 0; rb < RA; ++rb)
 #pragma unroll
-            for (int rb = 0; rb < RA; ++rb)
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-                    acc[rb][cb] = __builtin_amdgcn_mfma_i32_16x16x32_i8(
-                        fa[u][rb], fb[u][cb], v4i{kBiasBits, kBiasBits, kBiasBits, kBiasBits}, 0, 0, 0);
-            const uint32_t next = t + U * stride;
-            if (next < T) fetch(next, u);
-            uint32_t ta, tb;
-            tile_coords_lg(t, lgA, lgB, ta, tb);
-            const uint64_t baseC = (pdep_from(ta, ex.hiA) | pdep_from(tb, ex.hiB)) | waveC;
-            store_tile8<RA, CB, RED_BIAS>(acc, C, baseC, a, ex, ms, lane, wstage);
-        }
-        tile += U * stride;
-        if (tile >= T) break;
+            for (int cb = 0; cb < CB; ++cb)
+                acc[rb][cb] = __builtin_amdgcn_mfma_i32_16x16x32_i8(
+                    fa[rb], fb[cb], v4i{kBiasBits, kBiasBits, kBiasBits, kBiasBits}, 0, 0, 0);
+        const uint32_t next = tile + gridDim.x;
+        if (next < T) fetch(next);
+        uint32_t ta, tb;
+        tile_coords_lg(tile, lgA, lgB, ta, tb);
+        const uint64_t baseC = (pdep_from(ta, ex.hiA) | pdep_from(tb, ex.hiB)) | waveC;
+        store_tile8<RA, CB, RED_BIAS>(acc, C, baseC, a, ex, ms, lane, wstage);
+        if (next >= T) break;
+        tile = next;
     }
 }
 
@@ -856,7 +847,6 @@ Mfma8Extra extra_of(const StepArgs& a) {
 // A grid that fills the GPU once: the work-groups walk the tiles of every
 // plane, so that only their first tile waits for its first stages unhidden
 // (launched per plane with 1024 work-groups, a group had 4 to 32 tiles).
-
 template <class Gm, int NST, int RED>
 void launch_nst(const StepArgs& a, const Mfma8Extra& ex, int G, uint64_t T, int splits, int8_t* part,
                int64_t scratch_per_plane, hipStream_t stream) {
