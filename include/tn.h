@@ -293,7 +293,9 @@ tn_status tn_count_batch(const tn_formula* fs, int32_t n, tn_order_kind kind, ui
  * of 1 (small-modulus residues), 4 or 8 bytes and 2^(rA + rB - s)
  * multiply-adds per step and residue plane. */
 typedef enum {
-    TN_KC_GENERIC = 0, TN_KC_STREAM = 1, TN_KC_ROWDOT = 2, TN_KC_MFMA = 3, TN_KC_BATCH = 4, TN_KC_DOT = 5,
+    TN_KC_GENERIC = 0, TN_KC_STREAM = 1, TN_KC_ROWDOT = 2, TN_KC_MFMA = 3,
+    TN_KC_BATCH = 4,   /* small steps as programs, many in one launch (step shape 0) */
+    TN_KC_DOT = 5,
     TN_KC_DIGITS = 6,  /* in-place digit pass before TN_KC_MFMA */
     TN_KC_NARROW = 7   /* int8 matrix cores, B side of at most 64 rows: streams A once */
 } tn_kernel_class;

@@ -12,10 +12,10 @@
 // column l % 16 at K index l / 16 of a step), 16 x 16 blocks per wave, with the
 // weights of a wave's 32 columns kept in registers over all of its rows. What
 // is left bounds a training step: six launches, each little more than its
-// latency at 13 k rows (the longest: k_back1 22, k_forward 17, k_back2 13 us). Measured (MI355X, 13.4 k rows, 64 groups): forward +
-// backward + Adam 716 us with one-output-per-thread products and atomic sums
-// of every weight gradient, 61 us now; forward of 201 rows 37.7 us in three
-// launches, 6.8 us in one.
+// latency at 13 k rows (the longest: k_back1 24, k_forward 17, k_back2 15 us).
+// Measured (MI355X, 13.4 k rows, 64 groups): forward + backward + Adam 717 us with
+// one-output-per-thread products and atomic sums of every weight gradient, 62 us
+// now; forward of 201 rows 37.8 us in three launches, 7.3 us in one.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

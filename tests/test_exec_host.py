@@ -12,7 +12,7 @@ PKG = os.path.join(ROOT, "paper_1805_00475_amd")
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def program(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("exec") / "exec_check")
     cmd = ["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
            os.path.join(ROOT, "tests", "cpp", "exec_check.cpp"), "-L", PKG, "-ltn", f"-Wl,-rpath,{PKG}", "-o", exe]
@@ -37,11 +37,11 @@ def _long(free):
     ("cvc-n90", I.cvc(90, 1), False),
     ("1in3-n20", I.small_1in3(1), False),
 ])
-def test_default_execution_is_kept(checker, tmp_path, name, f, lowered):
+def test_default_execution_is_kept(program, tmp_path, name, f, lowered):
     path = tmp_path / "f.txt"
     path.write_text(f"{f.n_vars} {len(f.clauses)}\n" +
                     "".join(f"{k} {len(c)} {' '.join(map(str, c))}\n" for k, c in f.clauses))
     # (4: the search of many orders, on two threads, one round)
-    r = subprocess.run([checker, str(path), "4", "2", "1"], capture_output=True, text=True, timeout=120)
+    r = subprocess.run([program, str(path), "4", "2", "1"], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout
     assert ("lowered" in r.stdout) == lowered, r.stdout

@@ -13,7 +13,7 @@ LDS = 160 << 10  # bytes a work-group may ask for on gfx950
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def program(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("fuse") / "fuse_check")
     cmd = ["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
            os.path.join(ROOT, "tests", "cpp", "fuse_check.cpp"), "-L", PKG, "-ltn", f"-Wl,-rpath,{PKG}", "-o", exe]
@@ -43,12 +43,12 @@ CASES = [
 
 @pytest.mark.parametrize("name,f", CASES, ids=[c[0] for c in CASES])
 @pytest.mark.parametrize("es", [1, 4, 8])
-def test_program_fits_lds(checker, tmp_path, name, f, es):
+def test_program_fits_lds(program, tmp_path, name, f, es):
     path = tmp_path / "f.txt"
     path.write_text(f"{f.n_vars} {len(f.clauses)}\n" +
                     "".join(f"{k} {len(c)} {' '.join(map(str, c))}\n" for k, c in f.clauses))
     for order in (0, 1):
-        r = subprocess.run([checker, str(path), str(order), str(es), "0"], capture_output=True, text=True, timeout=120)
+        r = subprocess.run([program, str(path), str(order), str(es), "0"], capture_output=True, text=True, timeout=120)
         assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout[-2000:]
         assert int(r.stdout.split(" lds ")[1].split(",")[0]) <= LDS, r.stdout
 
@@ -62,14 +62,14 @@ def _chains(blocks):
     return f, 2 ** blocks * 267914296
 
 
-def test_chains_take_more_than_64_kib(checker, tmp_path):
+def test_chains_take_more_than_64_kib(program, tmp_path):
     # the formula of the GPU test below
     for es in (1, 4):
         f, _ = _chains(60)
         path = tmp_path / "f.txt"
         path.write_text(f"{f.n_vars} {len(f.clauses)}\n" +
                         "".join(f"{k} {len(c)} {' '.join(map(str, c))}\n" for k, c in f.clauses))
-        r = subprocess.run([checker, str(path), "0", str(es), "0"], capture_output=True, text=True, timeout=120)
+        r = subprocess.run([program, str(path), "0", str(es), "0"], capture_output=True, text=True, timeout=120)
         assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout[-2000:]
         assert 64 << 10 < int(r.stdout.split(" lds ")[1].split(",")[0]) <= LDS, r.stdout
 

@@ -12,7 +12,7 @@ PKG = os.path.join(ROOT, "paper_1805_00475_amd")
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def program(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("verify") / "verify_check")
     cmd = ["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
            os.path.join(ROOT, "tests", "cpp", "verify_check.cpp"), "-L", PKG, "-ltn", f"-Wl,-rpath,{PKG}", "-o", exe]
@@ -25,10 +25,10 @@ def checker(tmp_path_factory):
 @pytest.mark.parametrize("name,f", [("1in3-n20", I.small_1in3(1)), ("cvc-n60", I.cvc(60, 0)), ("cvc-n90", I.cvc(90, 3)),
                                     ("1in3-n110", I.large_1in3(110, 0.62, 4))])
 @pytest.mark.parametrize("es", [1, 4, 8])
-def test_verify_exec(checker, tmp_path, name, f, es):
+def test_verify_exec(program, tmp_path, name, f, es):
     path = tmp_path / "f.txt"
     path.write_text(f"{f.n_vars} {len(f.clauses)}\n" +
                     "".join(f"{k} {len(c)} {' '.join(map(str, c))}\n" for k, c in f.clauses))
     for order in (0, 1):
-        r = subprocess.run([checker, str(path), str(order), str(es)], capture_output=True, text=True, timeout=120)
+        r = subprocess.run([program, str(path), str(order), str(es)], capture_output=True, text=True, timeout=120)
         assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout[-2000:]
